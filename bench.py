@@ -174,19 +174,25 @@ def copy_ceiling(nbytes: int, reps: int = 10, all_variants: bool = False):
 
 
 # ---- rocprofv3 results -> profiles/traffic.json ------------------------------
-def _strip_count(nx, w):
-    """Strips of the step kernel's launch (same arithmetic as the library)."""
-    n = (nx + (w - 4) - 1) // (w - 4)
-    wo = (nx + n - 1) // n
-    return (nx + wo - 1) // wo
+def steps_per_launch(film, prec, launch):
+    """Time steps of one step_kernel launch of a film in round-to-nearest
+    mode: two for tau = 1 with FP32 arithmetic and segments of at least 6
+    (FP32 storage) or 16 rows (16-bit), else one (the library's rule)."""
+    two = film["tau"] == 1.0 and prec != "f64" and launch[1] >= (6 if prec == "f32" else 16)
+    return 2 if two else 1
 
 
-def step_grid_threads(film, launch):
-    """Work-items of one step_kernel dispatch of this film and launch shape
-    (the grid is padded to a multiple of the 8 XCDs)."""
+def step_grid_threads(film, prec, launch):
+    """Work-items of one step_kernel dispatch of this film and launch shape:
+    a wavefront per tile (54 columns where the film can take two steps per
+    launch, else 60, by seg_h rows), the grid padded to a multiple of the 8
+    XCDs."""
     w, sh = launch[0], launch[1]
-    tiles = _strip_count(film["nx"], w) * ((film["ny"] + sh - 1) // sh)
-    return (tiles + 7) // 8 * 8 * w
+    cols = 54 if film["tau"] == 1.0 and prec != "f64" else 60
+    n = -(-film["nx"] // cols)
+    strips = -(-film["nx"] // -(-film["nx"] // n))
+    groups = -(-strips * -(-film["ny"] // sh) // (w // 64))
+    return (groups + 7) // 8 * 8 * w
 
 
 def _read_csv(path):
@@ -204,17 +210,20 @@ def _find(dirname, suffix):
     raise FileNotFoundError(f"no *{suffix} under {dirname}")
 
 
-def _step_rows(rows, grid, warmup, steps, grid_key):
-    sel = [r for r in rows if "step_kernel" in r["Kernel_Name"] and int(r[grid_key]) == grid]
+def _step_rows(rows, grid, per, warmup, steps, grid_key):
+    """The dispatches of the last `steps` steps, `per` steps each (the
+    kernel's last template argument)."""
+    sel = [r for r in rows if "step_kernel" in r["Kernel_Name"] and int(r[grid_key]) == grid
+           and (f", {per}>" in r["Kernel_Name"] or f"ELi{per}EEE" in r["Kernel_Name"])]
     sel.sort(key=lambda r: int(r["Dispatch_Id"]) if "Dispatch_Id" in r else int(r["Start_Timestamp"]))
-    if len(sel) < warmup + steps:
-        raise ValueError(f"expected {warmup + steps} step_kernel dispatches of grid {grid}, found {len(sel)}")
-    return sel[len(sel) - steps:]
+    if len(sel) < warmup // per + steps // per:
+        raise ValueError(f"expected {warmup // per + steps // per} dispatches of grid {grid}, found {len(sel)}")
+    return sel[len(sel) - steps // per:]
 
 
-def _pmc_kib(dirname, grid, warmup, steps):
+def _pmc_kib(dirname, grid, per, warmup, steps):
     rows = _read_csv(_find(dirname, "counter_collection.csv"))
-    sel = _step_rows(rows, grid, warmup, steps, "Grid_Size")
+    sel = _step_rows(rows, grid, per, warmup, steps, "Grid_Size")
     return sum(float(r["Counter_Value"]) for r in sel) / len(sel)
 
 
@@ -242,19 +251,21 @@ def ingest_profile(a):
     film, _, spec = inputs.workload(a.workload)
     prec = a.precision or spec["precision"]
     launch = (a.block_w, a.seg_h, a.prefetch or 1)
-    grid = step_grid_threads(film, launch)
+    per = steps_per_launch(film, prec, launch)
+    grid = step_grid_threads(film, prec, launch)
     n_lu = film["n_layers"] * film["nx"] * film["ny"]
     bpl = mlfilm.bytes_per_update(prec)
-    alg = bpl * n_lu
-    kt = _step_rows(_read_csv(_find(a.ingest_kt, "kernel_trace.csv")), grid, a.warmup, a.steps, "Grid_Size_X")
+    alg = bpl * n_lu  # a launch reads and writes the populations once, whatever its steps
+    kt = _step_rows(_read_csv(_find(a.ingest_kt, "kernel_trace.csv")), grid, per, a.warmup, a.steps, "Grid_Size_X")
     dur = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3 for r in kt]  # us
-    fetch_kib = _pmc_kib(a.ingest_fetch, grid, a.warmup, a.steps)
-    write_kib = _pmc_kib(a.ingest_write, grid, a.warmup, a.steps)
+    fetch_kib = _pmc_kib(a.ingest_fetch, grid, per, a.warmup, a.steps)
+    write_kib = _pmc_kib(a.ingest_write, grid, per, a.warmup, a.steps)
     copy_bytes = n_lu * bpl // 2 // 16 * 16  # one population buffer, as bench.py --copy-probe
     fetch_scale = copy_bytes / (1024.0 * _copy_kib(a.ingest_fetch_copy, 2))
     write_scale = copy_bytes / (1024.0 * _copy_kib(a.ingest_write_copy, 2))
     fb, wb = fetch_kib * 1024 * fetch_scale, write_kib * 1024 * write_scale
-    ent = {"kernel_digest": kernel_digest(), "launch": list(launch), "hbm_bytes_per_launch": fb + wb,
+    ent = {"kernel_digest": kernel_digest(), "launch": list(launch), "steps_per_launch": per,
+           "hbm_bytes_per_launch": fb + wb,
            "fetch_bytes_per_launch": fb, "write_bytes_per_launch": wb, "fetch_scale": round(fetch_scale, 4),
            "write_scale": round(write_scale, 4), "algorithmic_bytes_per_launch": alg,
            "trace_us": {"dispatches": len(dur), "mean": statistics.fmean(dur), "median": statistics.median(dur),
@@ -343,7 +354,8 @@ def batch_point(args, steps, warm):
           f"each film's default shape", file=sys.stderr, flush=True)
 
     value = n_lu * steps / wall_b
-    achieved = 72 * n_lu / (kern_ms * 1e-3) / 1e9
+    per = steps_per_launch(films[0][0], "f32", launch)  # a launch moves the populations once
+    achieved = 72 * n_lu / (kern_ms * per * 1e-3) / 1e9
     out = {
         "metric": "batched scan: summed layer-lattice updates/s (one launch per step, graph-captured)",
         "value": value, "unit": "LU/s", "n_gpus": 1, "steps": steps, "warmup": warm,
@@ -357,7 +369,7 @@ def batch_point(args, steps, warm):
         "speedup_vs_plain": wall_p / wall_b,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None, "bytes_per_lu": 72,
-                     "kernel_ms": kern_ms},
+                     "kernel_ms": kern_ms * per, "steps_per_launch": per},
     }
     return out
 
@@ -566,18 +578,22 @@ def film_point(workload, prec, args, steps, warmup, lattice="d2q9"):
     del g
     torch.cuda.empty_cache()
     return {"film": film, "h0": h0, "n_lu": n_lu, "launch": launch, "source": source, "wall": wall,
-            "kern_ms": kern_ms, "pop_bytes": pop_bytes}
+            "kern_ms": kern_ms, "pop_bytes": pop_bytes,
+            "per_launch": 1 if d1 or args.rounding == "stochastic" else steps_per_launch(film, prec, launch)}
 
 
 def roofline_block(pt, workload, prec, working_set, copy):
     from paper_2409_16659_amd import mlfilm
 
     bpl = mlfilm.bytes_per_update(prec)
-    achieved = bpl * pt["n_lu"] / (pt["kern_ms"] * 1e-3) / 1e9
+    # one launch of `per` steps reads and writes the populations once
+    per = pt["per_launch"]
+    achieved = bpl * pt["n_lu"] / (pt["kern_ms"] * per * 1e-3) / 1e9
     out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": achieved / HBM_PEAK_GBS,
            "traffic": measured_traffic(workload, prec, pt["launch"]),
-           "bytes_per_lu": bpl, "lu_per_launch": pt["n_lu"], "kernel_ms": pt["kern_ms"],
+           "bytes_per_lu": bpl / per, "lu_per_launch": pt["n_lu"] * per, "kernel_ms": pt["kern_ms"] * per,
+           "steps_per_launch": per,
            "kernel": "step_kernel", "workload": workload, "launch": list(pt["launch"]),
            "working_set": working_set}
     if copy:

@@ -211,21 +211,23 @@ mlf_status mlf_load(mlf_handle* h, const void* blob, size_t bytes);
  *
  * Launch shape of the step kernel: block_w threads (64, 128, 192, 256 or 512;
  * 512 is MLF_EINVAL for FP64 films of four layers, whose kernel is compiled
- * for at most 256), one per column of a strip of block_w - 4 columns plus two
- * halo columns on each side, and seg_h rows per workgroup (>= 1).  Results
- * do not depend on the shape.  0 = default.  D1Q3 films keep their fixed
- * kernel shapes (the values are stored and ignored; mlf_autotune returns
- * them unchanged). */
+ * for at most 256), each wavefront of 64 taking one tile, a strip of 60
+ * columns (54 for films that can run two steps per launch: tau = 1, storage
+ * other than MLF_F64) by seg_h rows (>= 1).  Tall enough segments run two
+ * steps per launch.  Results do not depend on the shape.  0 = default,
+ * chosen by the film's size.  D1Q3 films keep their fixed kernel shapes
+ * (the values are stored and ignored; mlf_autotune returns them unchanged). */
 mlf_status mlf_set_launch(mlf_handle* h, int32_t block_w, int32_t seg_h);
 mlf_status mlf_get_launch(const mlf_handle* h, int32_t* block_w, int32_t* seg_h);
 
-/* Rows of populations the step kernel keeps in flight while it processes a
- * row: 1 (default; 0 selects it) or 2.  Two are available for D2Q9 films
- * with tau == 1 and storage other than MLF_F64 (FP32 arithmetic): they hide
- * more load latency on HBM-sized films at the cost of registers (fewer waves
- * per SIMD).  Results do not depend on it.  MLF_EINVAL for other values, or
- * for 2 on other films (mlf_last_error says why).  Drops a captured graph.
- * mlf_get_prefetch writes the current value (rows must not be NULL). */
+/* Rows of populations requested in flight: 1 (default; 0 selects it) or 2.
+ * Two are accepted for D2Q9 films with tau == 1 and storage other than
+ * MLF_F64.  The step kernel keeps one row in flight whatever is set here
+ * (its wavefronts are independent and cover each other's loads); the value
+ * is stored for programs that set it, and results do not depend on it.
+ * MLF_EINVAL for other values, or for 2 on other films (mlf_last_error says
+ * why).  Drops a captured graph.  mlf_get_prefetch writes the current value
+ * (rows must not be NULL). */
 mlf_status mlf_set_prefetch(mlf_handle* h, int32_t rows);
 mlf_status mlf_get_prefetch(const mlf_handle* h, int32_t* rows);
 
@@ -252,14 +254,13 @@ mlf_status mlf_get_rounding(const mlf_handle* h, int32_t* mode);
  * launched `reps` times (>= 1) from the current population buffer into the
  * other one without swapping, so the state and step counter are unchanged;
  * the four fastest are then re-timed twice with 4 x reps launches each and
- * the smallest time wins.  Candidates: block_w in {64, 128, 192, 256, 512}
- * (not 512 for FP64 films of four layers), segment heights from a fixed
- * list plus those that fill whole dispatch rounds of the device, and 1 or 2
- * rows in flight where mlf_set_prefetch allows 2 (the choice is kept; read
- * it with mlf_get_prefetch).  Synchronises. */
+ * the smallest time per step wins.  Candidates: block_w in {64, 128, 192,
+ * 256, 512} (not 512 for FP64 films of four layers), segment heights from a
+ * fixed list plus those that give one to four wavefronts per SIMD.
+ * Synchronises. */
 mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* seg_h);
 
-/* Capture `steps` (even, > 0) consecutive step launches into a HIP graph
+/* Capture the launches of `steps` (even, > 0) consecutive steps into a HIP graph
  * that mlf_step replays whenever at least `steps` steps remain (guard polls
  * then fall on replay boundaries); 0 drops it.  The graph holds the step
  * constants: mlf_init, mlf_init_device, mlf_load, mlf_set_launch and
@@ -279,8 +280,8 @@ mlf_status mlf_destroy(mlf_handle* h);
 
 /* ---- batches of independent films ------------------------------------
  * Many films (the paper's parameter sweeps over wavenumber, tension,
- * contact angle and layer count, Sec. IV) advanced together: every step
- * is ONE kernel launch over a work list of (film, tile) items, largest
+ * contact angle and layer count, Sec. IV) advanced together: every step (or
+ * pair of steps, as for one film) is ONE kernel launch over a work list of (film, tile) items, largest
  * film first, with each film's constants in a device table; films may
  * differ in size, layer count and every physical parameter but share the
  * precision, tau and the wetting exponents.  Results of each film are
@@ -319,13 +320,13 @@ mlf_status mlf_batch_init_device_all(mlf_batch* b, const double* const* hgts);
 mlf_status mlf_batch_init_device_all_u(mlf_batch* b, const double* const* hgts, const double* const* uxs,
                                        const double* const* uys);
 
-/* Advance every film by nsteps >= 0 steps: one launch per step, or replays
+/* Advance every film by nsteps >= 0 steps: one launch per step or pair of steps, or replays
  * of the captured graph where it fits.  The guard flags of all films are
  * read at the end; a tripped film gives ENONPOSITIVE / ENONFINITE and
  * mlf_batch_failed_film names it. */
 mlf_status mlf_batch_step(mlf_batch* b, int64_t nsteps);
 
-/* Capture `steps` (even, > 0) consecutive batch launches into a HIP graph
+/* Capture the launches of `steps` (even, > 0) consecutive steps into a HIP graph
  * that mlf_batch_step replays; 0 drops the graph.  Changing the launch
  * shape drops it too.  EUNSUPPORTED on the default stream and for D1Q3
  * batches. */
@@ -358,14 +359,15 @@ mlf_status mlf_batch_step_until(mlf_batch* b, int64_t max_steps, int32_t check_e
 /* Launch shape shared by all films: block_w in {64, 128, 192, 256}, seg_h
  * >= 1 rows (clamped to each film's ny), persistent != 0: as many
  * workgroups as fit the device at once, each taking work items in turn;
- * 0: one workgroup per item.  0 for block_w / seg_h selects 256 / 8.
+ * 0: one workgroup per item.  0 for block_w selects 256, for seg_h a height
+ * by the films' sizes.
  * EINVAL if the work list would exceed its scratch area. */
 mlf_status mlf_batch_set_launch(mlf_batch* b, int32_t block_w, int32_t seg_h, int32_t persistent);
 mlf_status mlf_batch_get_launch(const mlf_batch* b, int32_t* block_w, int32_t* seg_h, int32_t* persistent);
 
-/* Rows of populations in flight in the batch kernel, as mlf_set_prefetch
- * for a single film (2 only for D2Q9 batches with tau == 1 and storage
- * other than MLF_F64; results do not depend on it).  Drops a captured
+/* Rows of populations requested in flight, as mlf_set_prefetch for a single
+ * film (2 only for D2Q9 batches with tau == 1 and storage other than
+ * MLF_F64; stored, and without effect on the kernel or its results).  Drops a captured
  * graph.  rows must not be NULL for the getter. */
 mlf_status mlf_batch_set_prefetch(mlf_batch* b, int32_t rows);
 mlf_status mlf_batch_get_prefetch(const mlf_batch* b, int32_t* rows);
@@ -381,11 +383,9 @@ mlf_status mlf_batch_get_prefetch(const mlf_batch* b, int32_t* rows);
 mlf_status mlf_batch_set_rounding(mlf_batch* b, int32_t mode);
 mlf_status mlf_batch_get_rounding(const mlf_batch* b, int32_t* mode);
 
-/* Autotuner over block_w x seg_h x persistent x rows in flight (1, and 2
- * where mlf_batch_set_prefetch allows it), `reps` timed launches each from
- * the current buffer into the other (state unchanged); keeps the fastest
- * (read the depth with mlf_batch_get_prefetch).  Drops a captured graph.
- * Synchronises. */
+/* Autotuner over block_w x seg_h x persistent, `reps` timed launches each
+ * from the current buffer into the other (state unchanged); keeps the
+ * fastest per step.  Drops a captured graph.  Synchronises. */
 mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int32_t* seg_h, int32_t* persistent);
 
 /* Steps the batch has taken since it was created (-1 for NULL). */

@@ -4,9 +4,9 @@
 //
 // On one periodic row the populations moving north or south stream back
 // into the same row, and the stencils' north and south neighbours are the
-// node's own row; the arithmetic per node is that of the strip kernel
-// (same moment sums, the same pressure expressions, the shared
-// node_collide), so results are bit-identical to stepping the film with
+// node's own row; the arithmetic per node (row_moments, row_pressure,
+// row_collide) is that of row_tile, the step kernel's form for one-row
+// films, so results are bit-identical to stepping the film with
 // step_kernel.  One workgroup of up to 128 lanes, one node each (wider rows
 // take d2q9_row_tiled below); LDS holds the nine population planes, the
 // interface deviations and the pressures (11 N nx values).  Three barriers per step: every read
@@ -28,55 +28,6 @@ constexpr size_t kRowMaxLds = 160 * 1024;  // LDS of one workgroup on gfx950
 template <typename C>
 __host__ __device__ constexpr size_t row_resident_lds(int nx, int nl) {
   return (size_t)11 * nl * nx * sizeof(C);
-}
-
-// Pressures of one node from the interface deviations around it; the same
-// expressions as the strip kernel's pressure stage (z(i, r, c): interface
-// i + 1, row r, column c of the 3x3 neighbourhood).
-template <typename C, int NL, int EA, int EB, typename Z>
-__device__ inline void row_pressure(const StepConsts<C>& kc, Z&& z, C (&p)[NL]) {
-  C dzv[NL + 1], lap[NL + 1], qq[NL + 1];
-  dzv[0] = C(0);
-  qq[0] = C(0);
-  lap[0] = C(0);
-#pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const C sw = z(i, 0, 0), s = z(i, 0, 1), se = z(i, 0, 2);
-    const C wv = z(i, 1, 0), cc = z(i, 1, 1), e = z(i, 1, 2);
-    const C nw = z(i, 2, 0), nn = z(i, 2, 1), ne = z(i, 2, 2);
-    const C gx = (e - wv) * C(1.0 / 3.0) + ((ne + se) - (nw + sw)) * C(1.0 / 12.0);
-    const C gy = (nn - s) * C(1.0 / 3.0) + ((ne + nw) - (se + sw)) * C(1.0 / 12.0);
-    lap[i + 1] = (C(4) * ((e + wv) + (nn + s)) + ((ne + nw) + (se + sw)) - C(20) * cc) * C(1.0 / 6.0);
-    qq[i + 1] = gx * gx + gy * gy;
-    dzv[i + 1] = cc;
-  }
-  C sphi[NL + 1], dup[NL + 1], ddn[NL + 1];
-#pragma unroll
-  for (int i = 0; i <= NL; ++i) sphi[i] = dup[i] = ddn[i] = C(0);
-#pragma unroll
-  for (int l = 0; l < NL; ++l) {
-#pragma unroll
-    for (int kk = 1; kk <= NL - l; ++kk) {
-      if (!(kc.pairs >> (l * 4 + kk - 1) & 1u)) continue;
-      const C d = kc.dbar[l][kk - 1] + (dzv[l + kk] - dzv[l]);
-      const C rd = rcp(d);
-      const C rr = kc.khs[kk - 1] * rd;
-      C ra, rb;
-      pow_ab<EA, EB>(rr, kc, ra, rb);
-      C phi, dphi;
-      wetting<EA, EB>(kc, l, kk, ra, rb, rd, phi, dphi);
-      sphi[l] += phi;
-      dup[l] += dphi;
-      ddn[l + kk] += dphi * (C(1) + C(0.5) * qq[l]);
-    }
-  }
-  C acc = C(0);
-#pragma unroll
-  for (int i = NL; i >= 1; --i) {
-    const C delta = -(kc.gamma[i - 1] + sphi[i]) * lap[i] - dup[i] * (C(1) + C(0.5) * qq[i]) + ddn[i];
-    acc += delta;
-    p[i - 1] = acc;
-  }
 }
 
 // `steps` steps of one D2Q9 film with ny == 1, src -> (LDS) -> dst, FP64 or
@@ -119,10 +70,7 @@ d2q9_row_resident(const C* __restrict__ src, C* __restrict__ dst, const StepCons
         C dz = C(0);
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-          const C* ff = f[j][i];
-          dh[j][i] = ff[0] + ff[1] + ff[2] + ff[3] + ff[4] + ff[5] + ff[6] + ff[7] + ff[8];
-          qx[j][i] = (ff[1] + ff[2] + ff[8]) - (ff[4] + ff[5] + ff[6]);
-          qy[j][i] = (ff[2] + ff[3] + ff[4]) - (ff[6] + ff[7] + ff[8]);
+          row_moments(f[j][i], dh[j][i], qx[j][i], qy[j][i]);
           dz += dh[j][i];
           sz[x * NL + i] = dz;
           const C h = kc.hbar[i] + dh[j][i];
@@ -154,7 +102,7 @@ d2q9_row_resident(const C* __restrict__ src, C* __restrict__ dst, const StepCons
         const int cm = wrap(x - 1, nx), cp = wrap(x + 1, nx);
         auto pz = [&](int i, int, int c) { return sp[(c == 0 ? cm : (c == 1 ? x : cp)) * NL + i]; };
         C fo[NL][kQ];
-        node_collide<C, NL, TAU1>(kc, dh[j], qx[j], qy[j], pz, fo);
+        row_collide<C, NL, TAU1>(kc, dh[j], qx[j], qy[j], pz, fo);
 #pragma unroll
         for (int i = 0; i < NL; ++i)
 #pragma unroll
@@ -244,10 +192,7 @@ d2q9_row_tiled(const C* __restrict__ src, C* __restrict__ dst, const StepConsts<
       C dz = C(0);
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
-        const C* ff = f[i];
-        dh[i] = ff[0] + ff[1] + ff[2] + ff[3] + ff[4] + ff[5] + ff[6] + ff[7] + ff[8];
-        qx[i] = (ff[1] + ff[2] + ff[8]) - (ff[4] + ff[5] + ff[6]);
-        qy[i] = (ff[2] + ff[3] + ff[4]) - (ff[6] + ff[7] + ff[8]);
+        row_moments(f[i], dh[i], qx[i], qy[i]);
         dz += dh[i];
         sz[l * NL + i] = dz;
         if (owned) {
@@ -270,7 +215,7 @@ d2q9_row_tiled(const C* __restrict__ src, C* __restrict__ dst, const StepConsts<
     if (live) {
       auto pz = [&](int i, int, int c) { return sp[(c == 0 ? cm : (c == 1 ? l : cp)) * NL + i]; };
       C fo[NL][kQ];
-      node_collide<C, NL, TAU1>(kc, dh, qx, qy, pz, fo);
+      row_collide<C, NL, TAU1>(kc, dh, qx, qy, pz, fo);
 #pragma unroll
       for (int i = 0; i < NL; ++i)
 #pragma unroll

@@ -524,7 +524,7 @@ struct mlf_handle {
   double scale[kMaxLayers];  // storage scale per layer (1 except IEEE half)
   int64_t steps;
   int block_w, seg_h;
-  int ahead;  // rows of populations in flight in the step kernel (1 or 2)
+  int ahead;  // rows in flight asked for (mlf_set_prefetch; no effect on the kernel)
   int sr;     // stochastic rounding of the rest plane (16-bit storage)
   bool initialised;
   hipGraphExec_t graph;  // captured step loop (constants baked in), or null
@@ -644,10 +644,65 @@ double* redout_ptr(mlf_handle* h) { return reinterpret_cast<double*>(h->scratch 
 double* part_ptr(mlf_handle* h) { return reinterpret_cast<double*>(h->scratch + kPartOff); }
 unsigned char* stage_ptr(mlf_handle* h) { return h->scratch + kStageOff; }
 
+constexpr int kSimds = 1024;  // MI355X: 256 CUs of four SIMDs
+
+// Films whose step kernel can run two steps per launch: tau = 1 (the
+// post-collision state needs the moments only) with FP32 arithmetic (FP64
+// would need more registers than two waves per SIMD have).
+bool fusable(const mlf_params& p) { return p.lattice == MLF_D2Q9 && p.tau == 1.0 && p.precision != MLF_F64; }
+
+// Steps that the strips of a film are cut for (two-step strips also serve
+// single steps).
+int strip_steps(const mlf_params& p) { return fusable(p) ? 2 : 1; }
+
+// Smallest segment height from which two steps go into one launch.  A launch
+// of two steps moves the populations once instead of twice, but a segment
+// recomputes ten rows instead of four, so short segments (small films, which
+// take them to reach every SIMD) stay at one step: FP32, 3 layers, per step
+// at 384^2 (4 rows) 12.6 us against 13.6 us with two steps, at 512^2 (6 rows)
+// 16.2 / 16.0, 768^2 (12 rows) 26.0 / 22.5, 1024^2 (10 rows) 43 / 29.6; 16-bit
+// storage moves half the bytes for the same arithmetic and gains later:
+// f16mix, 4 layers, 768^2 (12 rows) 33.5 / 35.7, 1500^2 (21 rows) 94 / 80.
+int min_fused_rows(const mlf_params& p) { return p.precision == MLF_F32 ? 6 : 16; }
+
+// Segment height, for `tiles(height)` tiles over films of at most ny rows: the
+// lowest with at most one wavefront per SIMD, or, for films of two steps per
+// launch where that is above 12 rows, two (tall segments recompute little and
+// two wavefronts fill each other's waits; short ones recompute most of their
+// rows).  Even: the row loop takes two.  A tile more than fits costs a whole
+// second round: 4096^2, 3 layers, 542 us per step at 152 rows (2052 tiles),
+// 413 at 158 (1976).  FP64 wavefronts keep a SIMD busy alone: 1000^2, 3
+// layers, 119 us at 18 rows (969 tiles), 125 at 10 (1700).
+template <typename F>
+int seg_for(F&& tiles, int ny, bool two) {
+  auto lowest = [&](long long most) {
+    int sh = 2;
+    while (sh < ny && tiles(sh) > most) sh += 2;
+    return sh;
+  };
+  int sh = lowest(kSimds);
+  if (two && sh > 12) sh = lowest(2 * kSimds);
+  return std::max(1, std::min(sh, ny));
+}
+
+long long film_tiles(const mlf_params& p, int sh) {
+  return (long long)mlf::strip_count(p.nx, strip_steps(p)) * ((p.ny + sh - 1) / sh);
+}
+
+// Wavefronts per workgroup.  Neighbouring strips in one workgroup march
+// together and share the columns that both read, which pays where the film
+// streams from HBM: FP32, 4096^2, 3 layers, 388 us per step with eight, 412
+// with four, 570 with one.  16-bit storage is bound by arithmetic instead and
+// gains from tiles dealt out one by one (f16, 3 layers, 2900 x 2000: 151 us
+// with one, 168 with four), as do films with fewer tiles than SIMDs but more
+// than CUs (777 x 515, 3 layers, FP64: 43.5 / 47.2 us).
 void default_launch(const mlf_params* p, int* bw, int* sh) {
-  int w = p->nx + 4;
-  *bw = w <= 64 ? 64 : (w <= 128 ? 128 : (w <= 192 ? 192 : 256));
-  *sh = std::max(1, std::min(p->ny, 12));
+  *sh = seg_for([&](int s) { return film_tiles(*p, s); }, p->ny, fusable(*p));
+  const int nstrip = mlf::strip_count(p->nx, strip_steps(*p));
+  const long long t = film_tiles(*p, *sh);
+  if (nstrip < 4 || (t > kSimds / 4 && t <= kSimds)) *bw = 64;
+  else if (t <= kSimds || p->precision == MLF_F64) *bw = 256;
+  else *bw = p->precision == MLF_F32 ? 512 : 64;
 }
 
 template <typename C>
@@ -659,9 +714,8 @@ mlf::StepConsts<C> make_consts(const mlf_handle* h) {
   k.ny = p.ny;
   k.pitch = h->pitch;
   k.plane = (long long)h->plane;
-  const int W = h->block_w;
-  k.wout = mlf::strip_width(p.nx, W);
-  k.nstrip = mlf::strip_count(p.nx, W);
+  k.wout = mlf::strip_width(p.nx, strip_steps(p));
+  k.nstrip = mlf::strip_count(p.nx, strip_steps(p));
   k.seg_h = h->seg_h;
   k.nseg = (p.ny + k.seg_h - 1) / k.seg_h;
   const int n = p.n_layers;
@@ -701,74 +755,54 @@ mlf::StepConsts<C> make_consts(const mlf_handle* h) {
   return k;
 }
 
-// Workgroups of the step kernel that fit on one CU at the handle's block
-// width (0 if unknown).
-template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB, int AH>
-int occupancy_ah(const mlf_handle* h) {
-  int nb = 0;
-  size_t lds = (size_t)8 * NL * h->block_w * sizeof(C);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mlf::step_kernel<R, S, C, NL, T1, EA, EB, AH>, h->block_w,
-                                                   lds) != hipSuccess)
-    return 0;
-  return nb;
-}
-
-template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB, int AH>
-hipError_t launch_ah(const mlf_handle* h, const void* src, void* dst) {
+template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB, int STEPS>
+hipError_t launch_st(const mlf_handle* h, const void* src, void* dst) {
   mlf::StepConsts<C> kc = make_consts<C>(h);
+  const size_t nw = h->block_w / 64;
   // grid padded to a multiple of the XCD count (tile_of_block)
-  const int ntiles = kc.nstrip * kc.nseg;
-  const int nblocks = (ntiles + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
-  dim3 grid((unsigned)nblocks), block((unsigned)h->block_w);
-  size_t lds = (size_t)8 * NL * h->block_w * sizeof(C);
-  hipLaunchKernelGGL((mlf::step_kernel<R, S, C, NL, T1, EA, EB, AH>), grid, block, lds, h->stream,
-                     static_cast<const unsigned char*>(src), static_cast<unsigned char*>(dst), kc);
+  const int ngroups = (kc.nstrip * kc.nseg + (int)nw - 1) / (int)nw;
+  const int nblocks = (ngroups + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
+  if constexpr (std::is_same_v<R, C> && std::is_same_v<S, C>)
+    if (h->p.ny == 1) {
+      hipLaunchKernelGGL((mlf::row_step_kernel<C, NL, T1, EA, EB, STEPS>), dim3((unsigned)ngroups),
+                         dim3((unsigned)h->block_w), 0, h->stream, static_cast<const C*>(src), static_cast<C*>(dst),
+                         kc);
+      return hipGetLastError();
+    }
+  hipLaunchKernelGGL((mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS>), dim3((unsigned)nblocks),
+                     dim3((unsigned)h->block_w), nw * mlf::march_lds<C>(NL, STEPS), h->stream,
+                     static_cast<const unsigned char*>(src),
+                     static_cast<unsigned char*>(dst), kc);
   return hipGetLastError();
 }
 
-// Two rows ahead exist for tau = 1 with FP32 arithmetic only (prefetch_ok).
+// `steps` 2 only where fusable(h->p).
 template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB>
-int occupancy_nl(const mlf_handle* h) {
+hipError_t launch_nl(const mlf_handle* h, const void* src, void* dst, int steps) {
   if constexpr (T1 && sizeof(C) == 4)
-    if (h->ahead == 2) return occupancy_ah<R, S, C, NL, T1, EA, EB, 2>(h);
-  return occupancy_ah<R, S, C, NL, T1, EA, EB, 1>(h);
+    if (steps == 2) return launch_st<R, S, C, NL, T1, EA, EB, 2>(h, src, dst);
+  return launch_st<R, S, C, NL, T1, EA, EB, 1>(h, src, dst);
 }
 
-template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB>
-hipError_t launch_nl(const mlf_handle* h, const void* src, void* dst) {
-  if constexpr (T1 && sizeof(C) == 4)
-    if (h->ahead == 2) return launch_ah<R, S, C, NL, T1, EA, EB, 2>(h, src, dst);
-  return launch_ah<R, S, C, NL, T1, EA, EB, 1>(h, src, dst);
-}
-
-// Dispatch on (layers, tau == 1, exponents == (9, 3)); OCC selects the
-// occupancy query instead of a launch.
+// Dispatch on (layers, tau == 1, exponents == (9, 3)).
 template <typename R, typename S, typename C, bool T1, int EA, int EB>
-hipError_t launch_t(const mlf_handle* h, const void* src, void* dst, int* occ) {
+hipError_t launch_t(const mlf_handle* h, const void* src, void* dst, int steps) {
   switch (h->p.n_layers) {
-    case 1:
-      if (occ) return *occ = occupancy_nl<R, S, C, 1, T1, EA, EB>(h), hipSuccess;
-      return launch_nl<R, S, C, 1, T1, EA, EB>(h, src, dst);
-    case 2:
-      if (occ) return *occ = occupancy_nl<R, S, C, 2, T1, EA, EB>(h), hipSuccess;
-      return launch_nl<R, S, C, 2, T1, EA, EB>(h, src, dst);
-    case 3:
-      if (occ) return *occ = occupancy_nl<R, S, C, 3, T1, EA, EB>(h), hipSuccess;
-      return launch_nl<R, S, C, 3, T1, EA, EB>(h, src, dst);
-    default:
-      if (occ) return *occ = occupancy_nl<R, S, C, 4, T1, EA, EB>(h), hipSuccess;
-      return launch_nl<R, S, C, 4, T1, EA, EB>(h, src, dst);
+    case 1: return launch_nl<R, S, C, 1, T1, EA, EB>(h, src, dst, steps);
+    case 2: return launch_nl<R, S, C, 2, T1, EA, EB>(h, src, dst, steps);
+    case 3: return launch_nl<R, S, C, 3, T1, EA, EB>(h, src, dst, steps);
+    default: return launch_nl<R, S, C, 4, T1, EA, EB>(h, src, dst, steps);
   }
 }
 
 template <typename R, typename S, typename C>
-hipError_t launch_sc(const mlf_handle* h, const void* src, void* dst, int* occ) {
+hipError_t launch_sc(const mlf_handle* h, const void* src, void* dst, int steps) {
   const bool t1 = h->p.tau == 1.0;
   const bool e93 = h->p.exp_a == 9 && h->p.exp_b == 3;
-  if (t1 && e93) return launch_t<R, S, C, true, 9, 3>(h, src, dst, occ);
-  if (t1) return launch_t<R, S, C, true, 0, 0>(h, src, dst, occ);
-  if (e93) return launch_t<R, S, C, false, 9, 3>(h, src, dst, occ);
-  return launch_t<R, S, C, false, 0, 0>(h, src, dst, occ);
+  if (t1 && e93) return launch_t<R, S, C, true, 9, 3>(h, src, dst, steps);
+  if (t1) return launch_t<R, S, C, true, 0, 0>(h, src, dst, steps);
+  if (e93) return launch_t<R, S, C, false, 9, 3>(h, src, dst, steps);
+  return launch_t<R, S, C, false, 0, 0>(h, src, dst, steps);
 }
 
 // Calls f with typed null pointers of the handle's rest-plane and
@@ -785,13 +819,20 @@ void by_storage(const mlf_handle* h, F&& f) {
   }
 }
 
-hipError_t launch_step(const mlf_handle* h, const void* src, void* dst) {
+// Steps of the next launch of a film with `left` steps to go: two where the
+// film can (stochastic rounding draws on every step's count and stays at
+// one) and the segments are tall enough for it.
+int launch_steps(const mlf_handle* h, int64_t left) {
+  return left >= 2 && fusable(h->p) && !h->sr && h->seg_h >= min_fused_rows(h->p) ? 2 : 1;
+}
+
+hipError_t launch_step(const mlf_handle* h, const void* src, void* dst, int steps) {
   hipError_t e = hipSuccess;
   by_storage(h, [&](auto* rt, auto* st) {
     using R = std::remove_pointer_t<decltype(rt)>;
     using S = std::remove_pointer_t<decltype(st)>;
     using C = std::conditional_t<std::is_same_v<S, double>, double, float>;
-    e = launch_sc<R, S, C>(h, src, dst, nullptr);
+    e = launch_sc<R, S, C>(h, src, dst, steps);
   });
   return e;
 }
@@ -938,17 +979,6 @@ hipError_t row_advance_c(mlf_handle* h, int steps) {
 
 hipError_t row_advance(mlf_handle* h, int steps) {
   return h->p.precision == MLF_F64 ? row_advance_c<double>(h, steps) : row_advance_c<float>(h, steps);
-}
-
-int step_occupancy(const mlf_handle* h) {
-  int occ = 0;
-  by_storage(h, [&](auto* rt, auto* st) {
-    using R = std::remove_pointer_t<decltype(rt)>;
-    using S = std::remove_pointer_t<decltype(st)>;
-    using C = std::conditional_t<std::is_same_v<S, double>, double, float>;
-    (void)launch_sc<R, S, C>(h, nullptr, nullptr, &occ);  // occupancy query; 0 on error
-  });
-  return occ;
 }
 
 unsigned grid_for(long long n) {
@@ -1246,8 +1276,8 @@ mlf_status mlf_get_launch(const mlf_handle* h, int32_t* block_w, int32_t* seg_h)
   return MLF_OK;
 }
 
-// Two rows of populations in flight: D2Q9 films with tau = 1 and FP32
-// arithmetic (every storage format but FP64).
+// Two rows of populations in flight are accepted for D2Q9 films with tau = 1
+// and FP32 arithmetic (every storage format but FP64).
 bool prefetch_ok(const mlf_params& p) {
   return p.lattice == MLF_D2Q9 && p.tau == 1.0 && p.precision != MLF_F64;
 }
@@ -1296,52 +1326,44 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
   }
   drop_single_graph(h);
   const mlf_params& p = h->p;
-  int dev = 0, ncu = 0;
-  HIPCHK(hipGetDevice(&dev));
-  HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  const int keep_w = h->block_w, keep_h = h->seg_h, keep_a = h->ahead;
-  // candidates (block width, segment height, rows in flight)
-  typedef std::array<int, 3> Cand;
+  const int keep_w = h->block_w, keep_h = h->seg_h;
+  // candidates (block width, segment height)
+  typedef std::array<int, 2> Cand;
   std::vector<Cand> cand;
   const int fixed[] = {2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 128};
-  for (int ah = 1; ah <= (prefetch_ok(p) ? 2 : 1); ++ah)
-    for (int w : {64, 128, 192, 256, 512}) {
-      if (w > max_block_w(p)) continue;
-      h->block_w = w;
-      h->ahead = ah;
-      const int nstrip = mlf::strip_count(p.nx, w);
-      for (int sh : fixed)
-        if (sh <= p.ny) cand.push_back({w, sh, ah});
-      // heights that fill 1..4 whole dispatch rounds
-      const int slots = std::max(1, step_occupancy(h)) * std::max(1, ncu);
-      for (int rounds = 1; rounds <= 4; ++rounds) {
-        const int segs = std::max(1, rounds * slots / nstrip);
-        const int sh = std::max(1, (p.ny + segs - 1) / segs);
-        cand.push_back({w, std::min(sh, p.ny), ah});
-      }
+  const int nstrip = mlf::strip_count(p.nx, strip_steps(p));
+  for (int w : {64, 128, 192, 256, 512}) {
+    if (w > max_block_w(p)) continue;
+    for (int sh : fixed)
+      if (sh <= p.ny) cand.push_back({w, sh});
+    // heights that give one to four wavefronts per SIMD
+    for (int per = 1; per <= 4; ++per) {
+      const int segs = std::max(1, per * kSimds / nstrip);
+      cand.push_back({w, std::min(std::max(1, (p.ny + segs - 1) / segs), p.ny)});
     }
+  }
   std::sort(cand.begin(), cand.end());
   cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   mlf_status st = MLF_OK;
-  // ms per launch of candidate c over n launches (current -> other buffer,
+  // ms per step of candidate c over n launches (current -> other buffer,
   // never swapped: the state is left unchanged)
   auto time_of = [&](const Cand& c, int n, float* ms) {
     h->block_w = c[0];
     h->seg_h = c[1];
-    h->ahead = c[2];
-    if ((st = hip_check(h, launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1]), "autotune launch")) != MLF_OK)
+    const int adv = launch_steps(h, 2);
+    if ((st = hip_check(h, launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1], adv), "autotune launch")) != MLF_OK)
       return false;
     if ((st = hip_check(h, hipEventRecord(e0, h->stream), "hipEventRecord")) != MLF_OK) return false;
     for (int r = 0; r < n && st == MLF_OK; ++r)
-      st = hip_check(h, launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1]), "autotune launch");
+      st = hip_check(h, launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1], adv), "autotune launch");
     if (st != MLF_OK) return false;
     if ((st = hip_check(h, hipEventRecord(e1, h->stream), "hipEventRecord")) != MLF_OK) return false;
     if ((st = hip_check(h, hipEventSynchronize(e1), "hipEventSynchronize")) != MLF_OK) return false;
     if ((st = hip_check(h, hipEventElapsedTime(ms, e0, e1), "hipEventElapsedTime")) != MLF_OK) return false;
-    *ms /= (float)n;
+    *ms /= (float)(n * adv);
     return true;
   };
   // a first pass over every candidate, then the four fastest re-timed in two
@@ -1353,7 +1375,7 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
     if (!time_of(c, reps, &ms)) break;
     timed.emplace_back(ms, c);
   }
-  int bw = keep_w, bh = keep_h, ba = keep_a;
+  int bw = keep_w, bh = keep_h;
   if (st == MLF_OK && !timed.empty()) {
     std::sort(timed.begin(), timed.end());
     timed.resize(std::min<size_t>(timed.size(), 4));
@@ -1366,13 +1388,11 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
     const size_t k = (size_t)(std::min_element(best.begin(), best.end()) - best.begin());
     bw = timed[k].second[0];
     bh = timed[k].second[1];
-    ba = timed[k].second[2];
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   h->block_w = (st == MLF_OK) ? bw : keep_w;
   h->seg_h = (st == MLF_OK) ? bh : keep_h;
-  h->ahead = (st == MLF_OK) ? ba : keep_a;
   if (st != MLF_OK) return st;
   if (block_w) *block_w = bw;
   if (seg_h) *seg_h = bh;
@@ -1492,7 +1512,9 @@ mlf_status mlf_step(mlf_handle* h, int64_t nsteps) {
       HIPCHK(hipGraphLaunch(h->graph, h->stream));
       adv = h->graph_steps;
     } else {
-      HIPCHK(launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1]));
+      // two steps in one launch, but no further than the next guard poll
+      adv = launch_steps(h, every > 0 ? std::min<int64_t>(left, every - since) : left);
+      HIPCHK(launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1], (int)adv));
       h->cur ^= 1;
     }
     left -= adv;
@@ -1521,9 +1543,13 @@ mlf_status mlf_capture(mlf_handle* h, int32_t steps) {
   if (!h->stream) return fail(h, MLF_EUNSUPPORTED, "graph capture needs a non-default stream");
   HIPCHK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
   hipError_t le = hipSuccess;
-  for (int t = 0; t < steps && le == hipSuccess; ++t) {
-    const int c = (h->cur + t) & 1;
-    le = launch_step(h, h->pop[c], h->pop[c ^ 1]);
+  // an even number of launches, so that a replay leaves `cur` as it is: the
+  // last two steps take a launch each where their number is odd in pairs
+  int c = h->cur;
+  for (int left = steps; left > 0 && le == hipSuccess; c ^= 1) {
+    const int adv = steps % 4 == 2 && left <= 2 ? 1 : launch_steps(h, left);
+    le = launch_step(h, h->pop[c], h->pop[c ^ 1], adv);
+    left -= adv;
   }
   hipGraph_t g = nullptr;
   hipError_t ee = hipStreamEndCapture(h->stream, &g);
@@ -1828,7 +1854,8 @@ constexpr size_t kBatchFlagOff = (kScratchBytes + 255) / 256 * 256;        // in
 constexpr size_t kBatchTableOff = kBatchFlagOff + kMaxFilms * sizeof(int);  // BatchFilm<C>[n]
 constexpr size_t kBatchTableBytes = 4u << 20;
 constexpr size_t kBatchItemOff = kBatchTableOff + kBatchTableBytes;         // int2[n_items]
-constexpr size_t kBatchItemBytes = 12u << 20;
+constexpr long long kMaxTileUnits = (12u << 20) / sizeof(int2);  // largest launch accepted (batch_shape_ok)
+constexpr size_t kBatchItemBytes = 24u << 20;
 constexpr size_t kBatchSumOff = kBatchItemOff + kBatchItemBytes;          // double sums[kMaxFilms][4]
 constexpr size_t kBatchMinTabOff = kBatchSumOff + kMaxFilms * kMaxLayers * sizeof(double);  // MinFilm[n]
 constexpr size_t kBatchMinPartOff = kBatchMinTabOff + (kMaxFilms * sizeof(MinFilm) + 255) / 256 * 256;
@@ -1851,7 +1878,7 @@ struct mlf_batch {
   unsigned char* scratch;
   hipStream_t stream;
   int block_w, seg_h, persistent;
-  int ahead;  // rows of populations in flight in the batch kernel (1 or 2)
+  int ahead;  // rows in flight asked for (mlf_batch_set_prefetch; no effect on the kernel)
   int max_nl;
   int n_items;
   bool table_dirty;
@@ -1917,17 +1944,45 @@ size_t batch_table_entry(const mlf_batch* b) {
 
 int* batch_flags(mlf_batch* b) { return reinterpret_cast<int*>(b->scratch + kBatchFlagOff); }
 
-// Tiles of film f under the batch's launch shape.
+// Work items (workgroups) of film f under the batch's launch shape.
 long long film_tiles(const mlf_batch* b, int f, int bw, int sh) {
   const mlf_params& p = b->film[f]->p;
   const int s = std::min(sh, p.ny);
-  return (long long)mlf::strip_count(p.nx, bw) * ((p.ny + s - 1) / s);
+  const int nw = bw / 64;
+  return (film_tiles(p, s) + nw - 1) / nw;
 }
 
 long long batch_items(const mlf_batch* b, int bw, int sh) {
   long long t = 0;
   for (int f = 0; f < b->n; ++f) t += film_tiles(b, f, bw, sh);
   return t;
+}
+
+// Default segment height of a batch: the films' tiles together fill the
+// device as one film's do.
+int batch_default_seg(const mlf_batch* b) {
+  int ny = 1;
+  for (const mlf_handle* h : b->film) ny = std::max(ny, h->p.ny);
+  auto tiles = [&](int s) {
+    long long t = 0;
+    for (const mlf_handle* h : b->film) t += film_tiles(h->p, s);
+    return t;
+  };
+  return seg_for(tiles, ny, fusable(b->p0));
+}
+
+// Whether a launch shape is accepted: its tiles, counted as one per bw - 4
+// columns and sh rows, are at most kMaxTileUnits.  A workgroup's strips
+// cover at least half as many columns (54 of 64 lanes at two steps per
+// launch), so the work list takes at most twice that and always fits.
+bool batch_shape_ok(const mlf_batch* b, int bw, int sh) {
+  long long t = 0;
+  for (int f = 0; f < b->n; ++f) {
+    const mlf_params& p = b->film[f]->p;
+    const int s = std::min(sh, p.ny);
+    t += (long long)((p.nx + bw - 5) / (bw - 4)) * ((p.ny + s - 1) / s);
+  }
+  return t <= kMaxTileUnits;
 }
 
 // Device table and work list for the current launch shape (synchronous).
@@ -1947,7 +2002,7 @@ mlf_status upload_table_t(mlf_batch* b) {
     tab[f].nl = h->p.n_layers;
   }
   for (int f : b->order) {
-    const int nt = tab[f].kc.nstrip * tab[f].kc.nseg;
+    const int nt = (int)film_tiles(b, f, b->block_w, b->seg_h);
     for (int t = 0; t < nt; ++t) items.push_back(make_int2(f, t));
   }
   BHIPCHK(hipMemcpyAsync(b->scratch + kBatchTableOff, tab.data(), tab.size() * sizeof(tab[0]),
@@ -1965,16 +2020,10 @@ mlf_status upload_table(mlf_batch* b) {
   return batch_double(b) ? upload_table_t<double>(b) : upload_table_t<float>(b);
 }
 
-template <typename R, typename S, typename C, bool T1, int EA, int EB, int AH>
-hipError_t launch_batch_ah(const mlf_batch* b, int flip, int* occ) {
-  auto kern = mlf::batch_kernel<R, S, C, T1, EA, EB, AH>;
-  const size_t lds = (size_t)8 * b->max_nl * b->block_w * sizeof(C);
-  if (occ) {
-    int nb = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, b->block_w, lds);
-    *occ = nb;
-    return e;
-  }
+template <typename R, typename S, typename C, bool T1, int EA, int EB, int STEPS>
+hipError_t launch_batch_st(const mlf_batch* b, int flip) {
+  auto kern = mlf::batch_kernel<R, S, C, T1, EA, EB, STEPS>;
+  const size_t lds = b->block_w / 64 * mlf::march_lds<C>(kMaxLayers, STEPS);
   int grid = (b->n_items + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
   if (b->persistent) {
     int nb = 0, dev = 0, ncu = 0;
@@ -1993,23 +2042,22 @@ hipError_t launch_batch_ah(const mlf_batch* b, int flip, int* occ) {
 }
 
 template <typename R, typename S, typename C, bool T1, int EA, int EB>
-hipError_t launch_batch_t(const mlf_batch* b, int flip, int* occ) {
+hipError_t launch_batch_t(const mlf_batch* b, int flip, int steps) {
   if constexpr (T1 && sizeof(C) == 4)
-    if (b->ahead == 2) return launch_batch_ah<R, S, C, T1, EA, EB, 2>(b, flip, occ);
-  return launch_batch_ah<R, S, C, T1, EA, EB, 1>(b, flip, occ);
+    if (steps == 2) return launch_batch_st<R, S, C, T1, EA, EB, 2>(b, flip);
+  return launch_batch_st<R, S, C, T1, EA, EB, 1>(b, flip);
 }
 
 template <typename R, typename S, typename C>
-hipError_t launch_batch_sc(const mlf_batch* b, int flip, int* occ) {
+hipError_t launch_batch_sc(const mlf_batch* b, int flip, int steps) {
   const bool t1 = b->p0.tau == 1.0;
   const bool e93 = b->p0.exp_a == 9 && b->p0.exp_b == 3;
-  if (t1 && e93) return launch_batch_t<R, S, C, true, 9, 3>(b, flip, occ);
-  if (t1) return launch_batch_t<R, S, C, true, 0, 0>(b, flip, occ);
-  if (e93) return launch_batch_t<R, S, C, false, 9, 3>(b, flip, occ);
-  return launch_batch_t<R, S, C, false, 0, 0>(b, flip, occ);
+  if (t1 && e93) return launch_batch_t<R, S, C, true, 9, 3>(b, flip, steps);
+  if (t1) return launch_batch_t<R, S, C, true, 0, 0>(b, flip, steps);
+  if (e93) return launch_batch_t<R, S, C, false, 9, 3>(b, flip, steps);
+  return launch_batch_t<R, S, C, false, 0, 0>(b, flip, steps);
 }
 
-// One step of every film from buffer `flip` into the other one.
 // D1Q3 batch: one workgroup per film, `steps` steps held in LDS.
 template <typename C, bool T1, int EA, int EB>
 hipError_t d1_batch_launch_t(const mlf_batch* b, int steps) {
@@ -2039,13 +2087,19 @@ hipError_t d1_batch_launch(const mlf_batch* b, int steps) {
   return b->p0.precision == MLF_F64 ? d1_batch_launch_c<double>(b, steps) : d1_batch_launch_c<float>(b, steps);
 }
 
-hipError_t launch_batch(const mlf_batch* b, int flip) {
+// Steps of the next launch of the batch (as launch_steps for one film).
+int batch_launch_steps(const mlf_batch* b, int64_t left) {
+  return left >= 2 && fusable(b->p0) && !b->film[0]->sr && b->seg_h >= min_fused_rows(b->p0) ? 2 : 1;
+}
+
+// `steps` steps of every film from buffer `flip` into the other one.
+hipError_t launch_batch(const mlf_batch* b, int flip, int steps) {
   hipError_t e = hipSuccess;
   by_storage(b->film[0], [&](auto* rt, auto* st) {
     using R = std::remove_pointer_t<decltype(rt)>;
     using S = std::remove_pointer_t<decltype(st)>;
     using C = std::conditional_t<std::is_same_v<S, double>, double, float>;
-    e = launch_batch_sc<R, S, C>(b, flip, nullptr);
+    e = launch_batch_sc<R, S, C>(b, flip, steps);
   });
   return e;
 }
@@ -2138,10 +2192,10 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
     return lu(a) > lu(c);
   });
   b->block_w = 256;
-  b->seg_h = 8;
+  b->seg_h = batch_default_seg(b);
   b->persistent = 0;
   b->ahead = 1;
-  if (batch_items(b, b->block_w, b->seg_h) * (long long)sizeof(int2) > (long long)kBatchItemBytes ||
+  if (!batch_shape_ok(b, 256, 8) ||
       (size_t)n * batch_table_entry(b) > kBatchTableBytes) {
     for (mlf_handle* g : b->film) mlf_destroy(g);
     delete b;
@@ -2286,10 +2340,11 @@ mlf_status mlf_batch_step(mlf_batch* b, int64_t nsteps) {
       left -= b->graph_steps;
       b->steps += b->graph_steps;
     } else {
-      BHIPCHK(launch_batch(b, b->cur));
+      const int adv = batch_launch_steps(b, left);
+      BHIPCHK(launch_batch(b, b->cur, adv));
       b->cur ^= 1;
-      left -= 1;
-      b->steps += 1;
+      left -= adv;
+      b->steps += adv;
     }
   }
   return batch_guard(b);
@@ -2309,7 +2364,13 @@ mlf_status mlf_batch_capture(mlf_batch* b, int32_t steps) {
   if (st != MLF_OK) return st;
   BHIPCHK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
   hipError_t le = hipSuccess;
-  for (int t = 0; t < steps && le == hipSuccess; ++t) le = launch_batch(b, (b->cur + t) & 1);
+  // an even number of launches, as in mlf_capture
+  int c = b->cur;
+  for (int left = steps; left > 0 && le == hipSuccess; c ^= 1) {
+    const int adv = steps % 4 == 2 && left <= 2 ? 1 : batch_launch_steps(b, left);
+    le = launch_batch(b, c, adv);
+    left -= adv;
+  }
   hipGraph_t g = nullptr;
   hipError_t ee = hipStreamEndCapture(b->stream, &g);
   if (le != hipSuccess || ee != hipSuccess) {
@@ -2431,11 +2492,11 @@ mlf_status mlf_batch_step_until(mlf_batch* b, int64_t max_steps, int32_t check_e
 
 mlf_status mlf_batch_set_launch(mlf_batch* b, int32_t block_w, int32_t seg_h, int32_t persistent) {
   if (!b) return MLF_EINVAL;
-  const int bw = block_w == 0 ? 256 : block_w, sh = seg_h == 0 ? 8 : seg_h;
+  const int bw = block_w == 0 ? 256 : block_w, sh = seg_h == 0 ? batch_default_seg(b) : seg_h;
   if (bw != 64 && bw != 128 && bw != 192 && bw != 256)
     return bfail(b, MLF_EINVAL, "block_w must be 64, 128, 192 or 256");
   if (sh < 1) return bfail(b, MLF_EINVAL, "seg_h must be >= 1");
-  if (batch_items(b, bw, sh) * (long long)sizeof(int2) > (long long)kBatchItemBytes)
+  if (!batch_shape_ok(b, bw, seg_h == 0 ? 8 : sh))
     return bfail(b, MLF_EINVAL, "launch shape gives too many work items");
   b->block_w = bw;
   b->seg_h = sh;
@@ -2499,39 +2560,37 @@ mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int3
     return MLF_OK;
   }
   drop_graph(b);
-  const int keep_w = b->block_w, keep_h = b->seg_h, keep_p = b->persistent, keep_a = b->ahead;
+  const int keep_w = b->block_w, keep_h = b->seg_h, keep_p = b->persistent;
   struct Cand {
-    int w, h, p, a;
+    int w, h, p;
   };
   std::vector<Cand> cand;
-  for (int a = 1; a <= (prefetch_ok(b->p0) ? 2 : 1); ++a)
-    for (int w : {64, 128, 192, 256})
-      for (int h : {2, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96})
-        for (int pp : {0, 1})
-          if (batch_items(b, w, h) * (long long)sizeof(int2) <= (long long)kBatchItemBytes)
-            cand.push_back({w, h, pp, a});
+  for (int w : {64, 128, 192, 256})
+    for (int h : {2, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96})
+      for (int pp : {0, 1})
+        if (batch_shape_ok(b, w, h)) cand.push_back({w, h, pp});
   hipEvent_t e0, e1;
   BHIPCHK(hipEventCreate(&e0));
   BHIPCHK(hipEventCreate(&e1));
   float best = 1e30f;
-  Cand pick{keep_w, keep_h, keep_p, keep_a};
+  Cand pick{keep_w, keep_h, keep_p};
   for (const Cand& c : cand) {
     b->block_w = c.w;
     b->seg_h = c.h;
     b->persistent = c.p;
-    b->ahead = c.a;
     if ((st = upload_table(b)) != MLF_OK) break;
+    const int adv = batch_launch_steps(b, 2);
     // current -> other buffer, never swapped: the state is left unchanged
-    if ((st = bhip(b, launch_batch(b, b->cur), "autotune launch")) != MLF_OK) break;
+    if ((st = bhip(b, launch_batch(b, b->cur, adv), "autotune launch")) != MLF_OK) break;
     if ((st = bhip(b, hipEventRecord(e0, b->stream), "hipEventRecord")) != MLF_OK) break;
-    for (int r = 0; r < reps && st == MLF_OK; ++r) st = bhip(b, launch_batch(b, b->cur), "autotune launch");
+    for (int r = 0; r < reps && st == MLF_OK; ++r) st = bhip(b, launch_batch(b, b->cur, adv), "autotune launch");
     if (st != MLF_OK) break;
     if ((st = bhip(b, hipEventRecord(e1, b->stream), "hipEventRecord")) != MLF_OK) break;
     if ((st = bhip(b, hipEventSynchronize(e1), "hipEventSynchronize")) != MLF_OK) break;
     float ms = 0.f;
     if ((st = bhip(b, hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime")) != MLF_OK) break;
-    if (ms < best) {
-      best = ms;
+    if (ms / adv < best) {
+      best = ms / adv;
       pick = c;
     }
   }
@@ -2541,12 +2600,10 @@ mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int3
     b->block_w = pick.w;
     b->seg_h = pick.h;
     b->persistent = pick.p;
-    b->ahead = pick.a;
   } else {
     b->block_w = keep_w;
     b->seg_h = keep_h;
     b->persistent = keep_p;
-    b->ahead = keep_a;
   }
   b->table_dirty = true;
   mlf_status up = upload_table(b);
