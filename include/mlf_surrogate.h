@@ -83,7 +83,7 @@ mlf_status mlf_nop_train_step(mlf_nop* m, int32_t batch, const float* h0, const 
 /* Event-timed average duration (ms) of one 3x3 convolution of the first
  * block on `batch` samples, `reps` launches each, on the activations as
  * they stand (run mlf_nop_predict first): ms[0] forward with the plain
- * epilogue (also the input-gradient kernel), ms[1] forward with the GELU
+ * epilogue, ms[1] forward with the GELU
  * epilogue, ms[2] forward with the residual epilogue, ms[3] weight
  * gradient.  ms: host float[4].  Overwrites the first block's activations
  * and scratch only.  Synchronises.  EINVAL for NULL pointers or reps < 1. */

@@ -1,10 +1,10 @@
 // nop_kernels.hpp -- matrix-core kernels of the convolutional
 // neural-operator surrogate (gfx950): BF16 MFMA implicit-GEMM 3x3 periodic
 // convolutions (forward with its GELU / residual epilogues, the input
-// gradient through the same kernel with flipped transposed weights, and
-// the weight gradient).  The FP32 VALU kernels around them (patch encoder,
-// pixel-shuffle decoder, GELU gradient, reductions, MSE, Adam) are in
-// surrogate.hip.
+// gradient through the same kernel with flipped transposed weights and the
+// GELU gradient, residual sum and bias-gradient sums in its epilogues, and
+// the weight gradient).  The FP32 kernels around them (patch encoder,
+// pixel-shuffle decoder, reductions, loss, Adam) are in surrogate.hip.
 //
 // Latent tensors are NHWC: [batch][gy][gx][C], C a multiple of 32, x
 // fastest after the channels; the grid is periodic in both directions.
@@ -44,13 +44,24 @@ __device__ inline float gelu_f(float a, float* dg) {
   return a * s;
 }
 
-// Epilogues of the forward convolution: v = products + bias, then
+// Epilogues of the convolution: v = products + bias, then
 //  kEpiPlain: out = v;
 //  kEpiGelu:  out = v (pre-activation, FP32), outb = bf16(gelu(v));
+//  kEpiGeluB: outb = bf16(gelu(v)) only (inference keeps no pre-activation);
 //  kEpiResid: out = res + v, outb = bf16(out)  (residual block output; res
 //             joins the accumulators partway through the products, in an
-//             order fixed per output channel).
-enum { kEpiPlain = 0, kEpiGelu = 1, kEpiResid = 2 };
+//             order fixed per output channel);
+//  kEpiGrad:  g = v gelu'(res), outb = bf16(g): the input gradient of a
+//             block's second convolution taken through its GELU (res the
+//             pre-activation), colp = column sums of g;
+//  kEpiAcc:   out = res + v after the products, outb = bf16(out) where given,
+//             colp = column sums of out: the gradient of the residual stream
+//             (out may be res).
+// The last two keep FP32 values in registers from the products to their
+// column sums (the bias gradients), which go to colp[row of 64 pixels][C],
+// one row per wavefront: separate passes for the GELU gradient, the addition,
+// the BF16 copy and the sums moved 770 MiB more per block at batch 64.
+enum { kEpiPlain = 0, kEpiGelu = 1, kEpiResid = 2, kEpiGeluB = 3, kEpiGrad = 4, kEpiAcc = 5 };
 
 __device__ inline bf16x8 ld8(const __bf16* p) {
   const u32x4v w = *reinterpret_cast<const u32x4v*>(p);
@@ -89,9 +100,9 @@ __device__ inline int swz(int row, int q) { return row * 64 + ((q ^ (row >> 1)) 
 template <int C, int CO, int WAVES, int EPI>
 __global__ void __launch_bounds__(64 * WAVES, 2) conv3x3_fwd(const __bf16* __restrict__ in,
                                                               const __bf16* __restrict__ w,
-                                                              const float* __restrict__ bias, float* __restrict__ out,
-                                                              const float* __restrict__ res, __bf16* __restrict__ outb,
-                                                              int gy, int gx) {
+                                                              const float* __restrict__ bias, float* out,
+                                                              const float* res, __bf16* __restrict__ outb,
+                                                              float* __restrict__ colp, int gy, int gx) {
   constexpr int NT = CO / 16, ROWS = WAVES + 2, PX = 66;
   constexpr int NXP = ROWS * PX * 4, NWP = 3 * CO * 4;  // 16-byte pieces: input rows, one offset row of weights
   constexpr int NXI = (NXP + 63) / 64, NWI = (NWP + 63) / 64;  // LDS-direct wave loads of 64 pieces
@@ -239,18 +250,53 @@ __global__ void __launch_bounds__(64 * WAVES, 2) conv3x3_fwd(const __bf16* __res
         for (int i = 0; i < 4; ++i) se[(16 * m + 4 * g + i) * ES + 16 * nn + r] = acc[m][n0 + nn][i] + bv;
     }
     __syncthreads();
+    constexpr bool kSums = EPI == kEpiGrad || EPI == kEpiAcc;
+    constexpr bool kRes = kSums;
+    f32x4 rr[kRes ? IT : 1];
+    if constexpr (kRes) {
+#pragma unroll
+      for (int k = 0; k < IT; ++k)
+        rr[k] = *reinterpret_cast<const f32x4*>(res + base + (long long)(p0 + P * k) * C + 16 * n0 + c4);
+    }
+    f32x4 cs = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
-      const f32x4 o = *reinterpret_cast<const f32x4*>(se + (p0 + P * k) * ES + c4);
+      f32x4 o = *reinterpret_cast<const f32x4*>(se + (p0 + P * k) * ES + c4);
       const long long e = base + (long long)(p0 + P * k) * C + 16 * n0 + c4;
-      *reinterpret_cast<f32x4*>(out + e) = o;
-      if constexpr (EPI != kEpiPlain) {
-        __bf16 q4[4];
+      if constexpr (EPI == kEpiGrad) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) q4[j] = (__bf16)(EPI == kEpiGelu ? gelu_f(o[j], nullptr) : o[j]);
-        typedef unsigned int u32x2e __attribute__((ext_vector_type(2)));
-        *reinterpret_cast<u32x2e*>(outb + e) = __builtin_bit_cast(u32x2e, q4);
+        for (int j = 0; j < 4; ++j) {
+          float d;
+          gelu_f(rr[k][j], &d);
+          o[j] = o[j] * d;
+        }
+      } else if constexpr (EPI == kEpiAcc) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = rr[k][j] + o[j];
       }
+      if constexpr (kSums) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cs[j] += o[j];
+      }
+      if constexpr (EPI != kEpiGrad && EPI != kEpiGeluB) *reinterpret_cast<f32x4*>(out + e) = o;
+      if constexpr (EPI != kEpiPlain) {
+        if (EPI != kEpiAcc || outb) {
+          __bf16 q4[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            q4[j] = (__bf16)(EPI == kEpiGelu || EPI == kEpiGeluB ? gelu_f(o[j], nullptr) : o[j]);
+          typedef unsigned int u32x2e __attribute__((ext_vector_type(2)));
+          *reinterpret_cast<u32x2e*>(outb + e) = __builtin_bit_cast(u32x2e, q4);
+        }
+      }
+    }
+    if constexpr (kSums) {  // lanes of one channel quad differ in the pixel only
+#pragma unroll
+      for (int off = Q; off < 64; off *= 2)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cs[j] += __shfl_xor(cs[j], off, 64);
+      if (lane < Q)
+        *reinterpret_cast<f32x4*>(colp + (pbase / (64 * C)) * C + cg * CO + 16 * n0 + c4) = cs;
     }
   }
 }

@@ -63,15 +63,6 @@ __global__ void __launch_bounds__(1024) plane_mean(const float* __restrict__ a, 
   if (threadIdx.x == 0) out[blockIdx.x] = red[0] / (float)n;
 }
 
-// y = (a - mean[plane]) * scale; grid row blockIdx.y = plane (no index division)
-__global__ void center_scale(const float* __restrict__ a, const float* __restrict__ mean, float* __restrict__ y,
-                             long long n_plane, float scale) {
-  const long long base = (long long)blockIdx.y * n_plane;
-  const float mu = mean[blockIdx.y];
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n_plane; t += (long long)gridDim.x * 256)
-    y[base + t] = (a[base + t] - mu) * scale;
-}
-
 // prediction tail: o = h + s * (d - mean[plane]), the decoder output made
 // mass-free and added to the input in one pass
 __global__ void sub_mean_axpy(const float* __restrict__ h, const float* __restrict__ d,
@@ -84,13 +75,6 @@ __global__ void sub_mean_axpy(const float* __restrict__ h, const float* __restri
   }
 }
 
-// target increment (h1 - h0) / s
-__global__ void target_inc(const float* __restrict__ h0, const float* __restrict__ h1, float* __restrict__ o,
-                           float inv_s, long long total) {
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < total; t += (long long)gridDim.x * 256)
-    o[t] = (h1[t] - h0[t]) * inv_s;
-}
-
 // Wave-local LDS hand-off: the lanes of one wave write, then read what
 // other lanes of the same wave wrote (no workgroup barrier is needed).
 __device__ inline void wave_sync() {
@@ -101,19 +85,20 @@ __device__ inline void wave_sync() {
 
 // patch layer into the latent grid:
 //   out[b][py][px][c] = bias[c] + sum_j W[j][c] P[b][i][4py+u][4px+v],  j = (i*4+u)*4+v
-// the patch encoder (P = x, bias = b_E, BF16 copy of the output) and the
-// decoder's input gradient (P = dD, W = W_D, no bias, FP32 only).  A wave
-// takes 64 latent pixels of one row (one per lane; coalesced patch loads)
-// and 32 channels, so the weights are the same for all its lanes (scalar
-// loads); the 64 x 32 outputs are transposed through LDS so that each store
-// writes whole 128-byte channel runs.  CENTER forms the encoder's input
-// (P - pmean[plane]) * pscale on the fly (the prediction path, which keeps
-// no copy of it).  Needs (batch gy gx) % 64 == 0.
-template <bool BF16, bool CENTER>
+// and its BF16 copy: the patch encoder (P = (h - mean) / s, W = E, bias = b_E)
+// and the decoder's input gradient (P = dD - mean, W = W_D, no bias, and with
+// SUMS its column sums, colp[row of 64 pixels][C]).  A wave takes 64 latent
+// pixels of one row (one per lane; coalesced patch loads) and 32 channels, so
+// the weights are the same for all its lanes (scalar loads); the 64 x 32
+// outputs are transposed through LDS so that each store writes whole 128-byte
+// channel runs.  P = (img - pmean[plane]) * pscale is formed on the fly.
+// Needs (batch gy gx) % 64 == 0.
+template <bool SUMS>
 __global__ void __launch_bounds__(256) patch_to_latent(const float* __restrict__ P, const float* __restrict__ W,
                                                        const float* __restrict__ bias, float* __restrict__ out,
-                                                       __bf16* __restrict__ outb, int nl, int ny, int nx, int C,
-                                                       int batch, const float* __restrict__ pmean, float pscale) {
+                                                       __bf16* __restrict__ outb, float* __restrict__ colp, int nl,
+                                                       int ny, int nx, int C, int batch,
+                                                       const float* __restrict__ pmean, float pscale) {
   constexpr int RS = 33;  // LDS row stride of a pixel's 32 outputs (odd: no bank conflicts)
   __shared__ float so[4][64 * RS];
   const int gy = ny / kPatch, gx = nx / kPatch;
@@ -135,10 +120,8 @@ __global__ void __launch_bounds__(256) patch_to_latent(const float* __restrict__
       for (int u = 0; u < kPatch; ++u) {
         float4 pv = *reinterpret_cast<const float4*>(
             P + (((long long)b * nl + i) * ny + kPatch * py + u) * nx + kPatch * px);
-        if constexpr (CENTER) {  // the encoder's input (P - mean of the plane) * scale, formed here
-          const float mu = pmean[b * nl + i];
-          pv = make_float4((pv.x - mu) * pscale, (pv.y - mu) * pscale, (pv.z - mu) * pscale, (pv.w - mu) * pscale);
-        }
+        const float mu = pmean[b * nl + i];
+        pv = make_float4((pv.x - mu) * pscale, (pv.y - mu) * pscale, (pv.z - mu) * pscale, (pv.w - mu) * pscale);
         const float ps[4] = {pv.x, pv.y, pv.z, pv.w};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -150,12 +133,18 @@ __global__ void __launch_bounds__(256) patch_to_latent(const float* __restrict__
 #pragma unroll
     for (int c = 0; c < 32; ++c) s[lane * RS + c] = acc[c];
     wave_sync();
+    float cs = 0.f;
 #pragma unroll
     for (int k = 0; k < 32; ++k) {
       const int p = 2 * k + (lane >> 5), ch = lane & 31;
       const float v = s[p * RS + ch];
       out[(pbase + p) * C + c0 + ch] = v;
-      if constexpr (BF16) outb[(pbase + p) * C + c0 + ch] = (__bf16)v;
+      outb[(pbase + p) * C + c0 + ch] = (__bf16)v;
+      if constexpr (SUMS) cs += v;
+    }
+    if constexpr (SUMS) {
+      cs += __shfl_xor(cs, 32, 64);
+      if (lane < 32) colp[(wv / groups) * C + c0 + lane] = cs;
     }
     wave_sync();  // reads done before the next pass overwrites the rows
   }
@@ -215,138 +204,113 @@ __global__ void __launch_bounds__(256) dec_fwd(const float* __restrict__ r, cons
         make_float4(acc[4 * u], acc[4 * u + 1], acc[4 * u + 2], acc[4 * u + 3]);
 }
 
-// partial outer-product sums over pixels for the patch layers:
-//   part[blk][j][c] = sum_{pix in slice} P[pix][j] Q[pix][c]
-// where P[pix][j] is value j of the 4x4 patch of latent pixel pix in a
-// full-resolution tensor (the encoder input, or the decoder output
-// gradient) and Q a latent tensor.  Chunks of 32 pixels are staged in LDS;
-// each thread accumulates an 8 x 4 tile of (j, c).  Requires 16N <= 64 and
-// C <= 128.
-__global__ void __launch_bounds__(256) patch_outer(const float* __restrict__ img, const float* __restrict__ lat,
-                                                   float* __restrict__ part, int nl, int ny, int nx, int C,
-                                                   long long npix) {
-  constexpr int CH = 32;
-  __shared__ float sp[CH][64];
-  __shared__ float sq[CH][128];
-  const int gy = ny / kPatch, gx = nx / kPatch, J = nl * kPatch * kPatch;
-  const long long per = (npix + gridDim.x - 1) / gridDim.x;
-  const long long p0 = blockIdx.x * per, p1 = min(npix, p0 + per);
-  const int jg = threadIdx.x / 32, cg = threadIdx.x % 32;  // j0 = 8 jg, c0 = 4 cg
-  float acc[8][4];
+// Weight (and, for the decoder, bias) gradients of the patch layers:
+//   part[blk][j][c] = sum_{pix of the block} P[pix][j] Q[pix][c],  and with
+//   SUMS part[blk][16 NL C + j] = sum P[pix][j],
+// P[pix][j] = (img - pmean[plane]) * pscale the 4x4 patch values of latent
+// pixel pix (j = 16 i + 4 u + v) and Q a latent tensor.  A wavefront takes
+// runs of 64 pixels of one latent row and accumulates all 16 NL x C products
+// on the FP32 matrix cores (v_mfma_f32_16x16x4_f32: FP32 inputs and sums), four
+// pixels per instruction, operands straight from global memory: lane l holds
+// patch value l % 16 and channels (C / 16)(l % 16) .. of pixel l / 16, so that
+// column r of channel tile n is channel (C / 16) r + n and every lane loads
+// whole 16-byte pieces.  The block's four wavefronts are summed through LDS.
+// Bound by the latent tensor's bytes: 134 MB at batch 64; with LDS-staged
+// VALU products 116 us, now 50 us.
+typedef float f32x4m __attribute__((ext_vector_type(4)));
+template <int NL, int C, bool SUMS>
+__global__ void __launch_bounds__(256, 2) patch_outer(const float* __restrict__ img, const float* __restrict__ pmean,
+                                                      float pscale, const float* __restrict__ lat,
+                                                      float* __restrict__ part, int ny, int nx, long long runs) {
+  constexpr int NT = C / 16, JC = 16 * NL * C;
+  __shared__ float red[NL * NT * 256 + 16 * NL];
+  const int lane = threadIdx.x & 63, r = lane & 15, k = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gx = nx / kPatch, gy = ny / kPatch;
+  f32x4m acc[NL][NT];
+  float ps[NL];
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+  for (int i = 0; i < NL; ++i) {
+    ps[i] = 0.f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[a][q] = 0.f;
-  for (long long q0 = p0; q0 < p1; q0 += CH) {
-    const int n = (int)min((long long)CH, p1 - q0);
-    // stage patches: 4-float rows (i, u) of each pixel
-    for (int t = threadIdx.x; t < n * nl * kPatch; t += 256) {
-      const int k = t / (nl * kPatch), iu = t % (nl * kPatch), i = iu / kPatch, u = iu % kPatch;
-      const long long pix = q0 + k;
-      const int px = (int)(pix % gx), py = (int)((pix / gx) % gy), b = (int)(pix / ((long long)gx * gy));
-      const float4 v = *reinterpret_cast<const float4*>(
-          img + (((long long)b * nl + i) * ny + kPatch * py + u) * nx + kPatch * px);
-      float* d = &sp[k][(i * kPatch + u) * kPatch];
-      d[0] = v.x, d[1] = v.y, d[2] = v.z, d[3] = v.w;
+    for (int n = 0; n < NT; ++n) acc[i][n] = f32x4m{0.f, 0.f, 0.f, 0.f};
+  }
+  const int xr = gx / 64;
+  for (long long run = blockIdx.x * 4LL + wave; run < runs; run += gridDim.x * 4LL) {
+    const int px0 = (int)(run % xr) * 64, py = (int)((run / xr) % gy);
+    const long long b = run / ((long long)xr * gy);
+    const float* ip = img + (b * NL * ny + kPatch * py + (r >> 2)) * (long long)nx + kPatch * (px0 + k) + (r & 3);
+    const float* lp = lat + (run * 64 + k) * C + NT * r;
+    float mu[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) mu[i] = pmean[b * NL + i];
+#pragma unroll 4
+    for (int s = 0; s < 16; ++s) {  // pixels px0 + 4 s + k
+      float a[NL], q[NT];
+#pragma unroll
+      for (int i = 0; i < NL; ++i) a[i] = (ip[(long long)i * ny * nx + 16 * s] - mu[i]) * pscale;
+#pragma unroll
+      for (int n = 0; n < NT; n += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(lp + (long long)4 * s * C + n);
+        q[n] = v.x, q[n + 1] = v.y, q[n + 2] = v.z, q[n + 3] = v.w;
+      }
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        if constexpr (SUMS) ps[i] += a[i];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], q[n], acc[i][n], 0, 0, 0);
+      }
     }
-    for (int t = threadIdx.x; t < n * (C / 4); t += 256) {
-      const int k = t / (C / 4), c4 = (t % (C / 4)) * 4;
-      const float4 v = *reinterpret_cast<const float4*>(lat + (q0 + k) * C + c4);
-      sq[k][c4] = v.x, sq[k][c4 + 1] = v.y, sq[k][c4 + 2] = v.z, sq[k][c4 + 3] = v.w;
+  }
+  if constexpr (SUMS) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      ps[i] += __shfl_xor(ps[i], 16, 64);
+      ps[i] += __shfl_xor(ps[i], 32, 64);
+    }
+  }
+  for (int w = 3; w >= 1; --w) {  // wavefronts 3, 2, 1 into wavefront 0, in this order
+    if (wave == w) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) red[((i * NT + n) * 4 + j) * 64 + lane] = acc[i][n][j];
+        if (SUMS && k == 0) red[NL * NT * 256 + 16 * i + r] = ps[i];
+      }
     }
     __syncthreads();
-    if (8 * jg < J && 4 * cg < C)
-      for (int k = 0; k < n; ++k) {
-        float pv[8], qv[4];
+    if (wave == 0) {
 #pragma unroll
-        for (int a = 0; a < 8; ++a) pv[a] = sp[k][8 * jg + a];
+      for (int i = 0; i < NL; ++i) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) qv[q] = sq[k][4 * cg + q];
+        for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int a = 0; a < 8; ++a)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[a][q] += pv[a] * qv[q];
+          for (int j = 0; j < 4; ++j) acc[i][n][j] += red[((i * NT + n) * 4 + j) * 64 + lane];
+        if (SUMS) ps[i] += red[NL * NT * 256 + 16 * i + r];
       }
+    }
     __syncthreads();
   }
-  float* o = part + (long long)blockIdx.x * J * C;
+  if (wave != 0) return;
+  float* o = part + (long long)blockIdx.x * (JC + (SUMS ? 16 * NL : 0));
+  // D: rows (patch values) 4 k + j, column r = channel NT r + n
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+  for (int i = 0; i < NL; ++i) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = 8 * jg + a, c = 4 * cg + q;
-      if (j < J && c < C) o[(long long)j * C + c] = acc[a][q];
-    }
-}
-
-// partial patch sums: part[blk][j] = sum_{pix in slice} P[pix][j], in pixel
-// order.  The pixel's (image, row, column) advance incrementally (no
-// division per pixel) and 8 pixels' loads are issued before they are added.
-__global__ void __launch_bounds__(256) patch_sum(const float* __restrict__ img, float* __restrict__ part, int nl,
-                                                 int ny, int nx, long long npix) {
-  const int gy = ny / kPatch, gx = nx / kPatch, J = nl * kPatch * kPatch;
-  const long long per = (npix + gridDim.x - 1) / gridDim.x;
-  const long long p0 = blockIdx.x * per, p1 = min(npix, p0 + per);
-  for (int j = threadIdx.x; j < J; j += 256) {
-    const int i = j / (kPatch * kPatch), u = (j / kPatch) % kPatch, v = j % kPatch;
-    float s = 0.f;
-    if (p0 < p1) {
-      int px = (int)(p0 % gx), py = (int)((p0 / gx) % gy);
-      long long b = p0 / ((long long)gx * gy);
-      auto addr = [&]() { return ((b * nl + i) * ny + kPatch * py + u) * nx + kPatch * px + v; };
-      auto next = [&]() {
-        if (++px == gx) {
-          px = 0;
-          if (++py == gy) {
-            py = 0;
-            ++b;
-          }
-        }
-      };
-      long long pix = p0;
-      for (; pix + 8 <= p1; pix += 8) {
-        float vv[8];
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          vv[q] = img[addr()];
-          next();
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) s += vv[q];
-      }
-      for (; pix < p1; ++pix) {
-        s += img[addr()];
-        next();
-      }
-    }
-    part[(long long)blockIdx.x * J + j] = s;
+      for (int n = 0; n < NT; n += 4)
+        *reinterpret_cast<float4*>(o + (long long)(16 * i + 4 * k + j) * C + NT * r + n) =
+            make_float4(acc[i][n][j], acc[i][n + 1][j], acc[i][n + 2][j], acc[i][n + 3][j]);
+    if (SUMS && k == 0) o[JC + 16 * i + r] = ps[i];
   }
 }
 
-// partial column sums: part[blk][c] = sum_{pix in slice} a[pix][c], in pixel
-// order; 8 rows' loads are issued together before they are added.
-__global__ void __launch_bounds__(256) col_partial(const float* __restrict__ a, float* __restrict__ part, int C,
-                                                   long long npix) {
-  const long long per = (npix + gridDim.x - 1) / gridDim.x;
-  const long long p0 = blockIdx.x * per, p1 = min(npix, p0 + per);
-  for (int c = threadIdx.x; c < C; c += 256) {
-    float s = 0.f;
-    long long pix = p0;
-    for (; pix + 8 <= p1; pix += 8) {
-      float v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = a[(pix + q) * C + c];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s += v[q];
-    }
-    for (; pix < p1; ++pix) s += a[pix * C + c];
-    part[(long long)blockIdx.x * C + c] = s;
-  }
-}
-
-// out[k] (+)= sum_r part[r][k]  (fixed order: r ascending; 8 rows' loads
-// are issued together before they are added)
-__global__ void sum_rows(const float* __restrict__ part, float* __restrict__ out, int rows, long long K, int add) {
+// out[k] = sum_r part[r][k] (fixed order: r ascending; 8 rows' loads are
+// issued together before they are added), for many columns
+__global__ void sum_rows(const float* __restrict__ part, float* __restrict__ out, int rows, long long K) {
   for (long long k = blockIdx.x * 256LL + threadIdx.x; k < K; k += (long long)gridDim.x * 256) {
     float s = 0.f;
     int r = 0;
@@ -358,35 +322,39 @@ __global__ void sum_rows(const float* __restrict__ part, float* __restrict__ out
       for (int q = 0; q < 8; ++q) s += v[q];
     }
     for (; r < rows; ++r) s += part[(long long)r * K + k];
-    out[k] = add ? out[k] + s : s;
+    out[k] = s;
   }
 }
 
-using nop::gelu_f;
-
-// da = dg * gelu'(a), FP32 and BF16
-__global__ void gelu_bwd(const float* __restrict__ dg, const float* __restrict__ a, float* __restrict__ da,
-                         __bf16* __restrict__ dab, long long n) {
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n; t += (long long)gridDim.x * 256) {
-    float d;
-    gelu_f(a[t], &d);
-    const float v = dg[t] * d;
-    da[t] = v;
-    dab[t] = (__bf16)v;
+// The same for few columns and many rows: a workgroup takes 8 columns, 128
+// row groups of them (rows g, g + 128, ...) side by side and then a tree in
+// LDS, so that the chain of dependent additions is rows / 128 long instead of
+// rows (K = 128, 512 rows, one thread per column: 32 us; now 4 us).
+constexpr int kFewCols = 8, kFewGroups = 128;
+__global__ void __launch_bounds__(kFewCols* kFewGroups) sum_rows_few(const float* __restrict__ part,
+                                                                     float* __restrict__ out, int rows, int K) {
+  __shared__ float red[kFewGroups][kFewCols];
+  const int c = threadIdx.x % kFewCols, g = threadIdx.x / kFewCols;
+  const int k = blockIdx.x * kFewCols + c;
+  float s = 0.f;
+  if (k < K) {
+    int r = g;
+    for (; r + 3 * kFewGroups < rows; r += 4 * kFewGroups) {
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = part[(long long)(r + q * kFewGroups) * K + k];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s += v[q];
+    }
+    for (; r < rows; r += kFewGroups) s += part[(long long)r * K + k];
   }
-}
-
-// y (+)= a; optional BF16 copy of the result
-__global__ void add_into(float* __restrict__ y, const float* __restrict__ a, __bf16* __restrict__ yb, long long n) {
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n; t += (long long)gridDim.x * 256) {
-    const float v = y[t] + a[t];
-    y[t] = v;
-    if (yb) yb[t] = (__bf16)v;
+  red[g][c] = s;
+  __syncthreads();
+  for (int w = kFewGroups / 2; w > 0; w >>= 1) {
+    if (g < w) red[g][c] += red[g + w][c];
+    __syncthreads();
   }
-}
-
-__global__ void to_bf16(const float* __restrict__ a, __bf16* __restrict__ b, long long n) {
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n; t += (long long)gridDim.x * 256) b[t] = (__bf16)a[t];
+  if (g == 0 && k < K) out[k] = red[0][c];
 }
 
 // BF16 conv weights: w[o][co][ci] and the flipped transpose wt[o][ci][co] = w[8-o][co][ci]
@@ -400,32 +368,50 @@ __global__ void conv_weights(const float* __restrict__ w, __bf16* __restrict__ w
   }
 }
 
-// d = d - mean[plane]
-__global__ void sub_plane_mean(float* __restrict__ d, const float* __restrict__ mean, long long n_plane) {
+// Loss and its gradient in one pass over the decoder output d, the plane means
+// that make it mass-free, and the heights: e = (d - mean) - (h1 - h0) inv_s,
+// grad = k e (where given), part[plane][block] = sum e^2.  Grid: (blocks, planes).
+constexpr int kLossBlocks = 16;  // per plane
+__global__ void __launch_bounds__(256) loss_grad(const float* __restrict__ d, const float* __restrict__ mean,
+                                                 const float* __restrict__ h0, const float* __restrict__ h1,
+                                                 float inv_s, float k, float* __restrict__ grad,
+                                                 float* __restrict__ part, long long n_plane) {
+  __shared__ float red[4];
   const long long base = (long long)blockIdx.y * n_plane;
   const float mu = mean[blockIdx.y];
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n_plane; t += (long long)gridDim.x * 256)
-    d[base + t] -= mu;
+  float s = 0.f;
+  for (long long t = (blockIdx.x * 256LL + threadIdx.x) * 4; t < n_plane; t += (long long)gridDim.x * 1024) {
+    const float4 dv = *reinterpret_cast<const float4*>(d + base + t);
+    const float4 a = *reinterpret_cast<const float4*>(h0 + base + t), b = *reinterpret_cast<const float4*>(h1 + base + t);
+    float4 g;
+    auto one = [&](float dd, float x0, float x1) {
+      const float free = dd - mu;
+      const float tgt = (x1 - x0) * inv_s;
+      const float e = free - tgt;
+      s += e * e;
+      return k * e;
+    };
+    g.x = one(dv.x, a.x, b.x);
+    g.y = one(dv.y, a.y, b.y);
+    g.z = one(dv.z, a.z, b.z);
+    g.w = one(dv.w, a.w, b.w);
+    if (grad) *reinterpret_cast<float4*>(grad + base + t) = g;
+  }
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// loss partials: part[blk] = sum (delta - target)^2 over a slice; grad = 2 (delta - target) / n
-__global__ void __launch_bounds__(256) mse(const float* __restrict__ d, const float* __restrict__ tgt,
-                                           float* __restrict__ grad, float* __restrict__ part, long long n) {
-  __shared__ float red[256];
-  float s = 0.f;
-  const float k = 2.f / (float)n;
-  for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n; t += (long long)gridDim.x * 256) {
-    const float e = d[t] - tgt[t];
-    s += e * e;
-    if (grad) grad[t] = k * e;
-  }
-  red[threadIdx.x] = s;
+// out = sum of n partials in FP64, fixed order (one workgroup)
+__global__ void __launch_bounds__(256) loss_finish(const float* __restrict__ part, double* __restrict__ out, int n) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int t = threadIdx.x; t < n; t += 256) s += part[t];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) out[0] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 __global__ void adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
@@ -520,9 +506,10 @@ struct mlf_nop {
   // workspace regions
   float *par, *grad, *am, *av;
   __bf16 *w1b, *w1t, *w2b, *w2t;  // [L][9][C][C]
-  float *x, *tgt, *D, *dD, *mean, *loss_part;
-  float *r, *a, *c, *dr, *tmp;   // r: [L+1][lat], a: [L][lat]
-  __bf16 *rb, *gb, *cb;          // rb: [L+1][lat], gb: [L][lat], cb: [lat]
+  float *D, *dD, *mean, *mean_h, *loss_part;  // mean: of D, then of dD; mean_h: of the input heights
+  double* loss;
+  float *r, *a, *dr;              // r: [L+1][lat], a: [L][lat], dr: [lat]
+  __bf16 *rb, *gb, *cb, *cb2;     // rb: [L+1][lat], gb: [L][lat], cb, cb2: [lat]
   float *part;
   long long lat, img;            // floats per latent tensor / per image batch tensor (max batch)
   long long part_floats;
@@ -591,18 +578,20 @@ Layout layout_of(const mlf_nop_params* p) {
   const long long gy = p->ny / kPatch, gx = p->nx / kPatch;
   s.lat = (long long)p->batch * gy * gx * C;
   s.img = (long long)p->batch * N * p->ny * p->nx;
-  s.part_floats = std::max<long long>({(long long)kWgSlices * 9 * C * C, (long long)kRedBlocks * J * C,
-                                       (long long)kRedBlocks * C, (long long)kRedBlocks});
+  s.part_floats = std::max<long long>({(long long)kWgSlices * 9 * C * C, (long long)kRedBlocks * (J * C + J),
+                                       (long long)kRedBlocks * J, s.lat / 64});
   // regions: floats then bf16, 256-byte aligned
   const long long npa = a64(s.npar);
   std::vector<long long> sz = {
       npa * 4, npa * 4, npa * 4, npa * 4,                                   // par grad am av
       a64(L * 9 * C * C) * 2 * 4,                                           // w1b w1t w2b w2t (bf16 each)
-      a64(s.img) * 4, a64(s.img) * 4, a64(s.img) * 4, a64(s.img) * 4,       // x tgt D dD
-      a64(p->batch * N) * 4, a64(kRedBlocks) * 4,                           // mean loss_part
+      a64(s.img) * 4, a64(s.img) * 4,                                       // D dD
+      a64(p->batch * N) * 4, a64(p->batch * N) * 4,                         // mean mean_h
+      a64(p->batch * N * kLossBlocks) * 4, 256,                             // loss_part loss
       a64((L + 1) * s.lat) * 4, a64(std::max(1LL, L) * s.lat) * 4,          // r a
-      a64(s.lat) * 4, a64(s.lat) * 4, a64(s.lat) * 4,                       // c dr tmp
-      a64((L + 1) * s.lat) * 2, a64(std::max(1LL, L) * s.lat) * 2, a64(s.lat) * 2,  // rb gb cb
+      a64(s.lat) * 4,                                                       // dr
+      a64((L + 1) * s.lat) * 2, a64(std::max(1LL, L) * s.lat) * 2,          // rb gb
+      a64(s.lat) * 2, a64(s.lat) * 2,                                       // cb cb2
       a64(s.part_floats) * 4};
   size_t o = 0;
   for (size_t i = 0; i < sz.size(); ++i) {
@@ -622,27 +611,27 @@ Layout layout_of(const mlf_nop_params* p) {
 // (set_lds_limits, on the handle's device).
 template <int C, int CO, int EPI>
 mlf_status conv_fwd_launch(mlf_nop* m, long long rows, const __bf16* in, const __bf16* w, const float* bias,
-                           float* out, const float* res, __bf16* outb) {
+                           float* out, const float* res, __bf16* outb, float* colp) {
   const size_t lds = nop::conv3x3_fwd_lds(CO, 4);
   const unsigned xt = (unsigned)(m->gx / 64);
   NLAUNCH((nop::conv3x3_fwd<C, CO, 4, EPI>), dim3((unsigned)(rows / 4) * xt, C / CO), dim3(256), lds, m->stream,
-          in, w, bias, out, res, outb, m->gy, m->gx);
+          in, w, bias, out, res, outb, colp, m->gy, m->gx);
   return MLF_OK;
 }
 
 template <int C, int EPI>
 mlf_status conv_fwd_t(mlf_nop* m, int batch, const __bf16* in, const __bf16* w, const float* bias, float* out,
-                      const float* res, __bf16* outb) {
+                      const float* res, __bf16* outb, float* colp) {
   const long long rows = (long long)batch * m->gy;
-  if (rows < 64 * 64) return conv_fwd_launch<C, 32, EPI>(m, rows, in, w, bias, out, res, outb);
-  return conv_fwd_launch<C, C, EPI>(m, rows, in, w, bias, out, res, outb);
+  if (rows < 64 * 64) return conv_fwd_launch<C, 32, EPI>(m, rows, in, w, bias, out, res, outb, colp);
+  return conv_fwd_launch<C, C, EPI>(m, rows, in, w, bias, out, res, outb, colp);
 }
 
 template <int EPI>
 mlf_status conv_fwd_e(mlf_nop* m, int batch, const __bf16* in, const __bf16* w, const float* bias, float* out,
-                      const float* res, __bf16* outb) {
-  return m->C == 64 ? conv_fwd_t<64, EPI>(m, batch, in, w, bias, out, res, outb)
-                    : conv_fwd_t<128, EPI>(m, batch, in, w, bias, out, res, outb);
+                      const float* res, __bf16* outb, float* colp = nullptr) {
+  return m->C == 64 ? conv_fwd_t<64, EPI>(m, batch, in, w, bias, out, res, outb, colp)
+                    : conv_fwd_t<128, EPI>(m, batch, in, w, bias, out, res, outb, colp);
 }
 
 mlf_status conv_fwd(mlf_nop* m, int batch, const __bf16* in, const __bf16* w, const float* bias, float* out) {
@@ -694,6 +683,9 @@ mlf_status set_lds_limits_c(mlf_nop* m) {
   mlf_status st = set_fwd_lds<C, nop::kEpiPlain>(m);
   if (st == MLF_OK) st = set_fwd_lds<C, nop::kEpiGelu>(m);
   if (st == MLF_OK) st = set_fwd_lds<C, nop::kEpiResid>(m);
+  if (st == MLF_OK) st = set_fwd_lds<C, nop::kEpiGeluB>(m);
+  if (st == MLF_OK) st = set_fwd_lds<C, nop::kEpiGrad>(m);
+  if (st == MLF_OK) st = set_fwd_lds<C, nop::kEpiAcc>(m);
   if (st == MLF_OK) st = set_lds(m, nop::conv3x3_wgrad<C, kWgW<C>, kWgW<C>>, nop::conv3x3_wgrad_lds(C));
   return st;
 }
@@ -705,15 +697,41 @@ mlf_status conv_wgrad(mlf_nop* m, int batch, const __bf16* in, const __bf16* dou
   const mlf_status st = m->C == 64 ? wgrad_launch<64>(m, batch, in, dout) : wgrad_launch<128>(m, batch, in, dout);
   if (st != MLF_OK) return st;
   const long long K = 9LL * m->C * m->C;
-  NLAUNCH(sum_rows, dim3(grid1(K)), dim3(256), 0, m->stream, m->part, dw, wgrad_slices(m, batch), K, 0);
+  NLAUNCH(sum_rows, dim3(grid1(K)), dim3(256), 0, m->stream, m->part, dw, wgrad_slices(m, batch), K);
   return MLF_OK;
 }
 
-// bias gradient: db[c] = sum over pixels of a[pix][c]
-mlf_status bias_grad(mlf_nop* m, long long npix, const float* a, float* db) {
-  NLAUNCH(col_partial, dim3(kRedBlocks), dim3(256), 0, m->stream, a, m->part, m->C, npix);
-  NLAUNCH(sum_rows, dim3(grid1(m->C)), dim3(256), 0, m->stream, m->part, db, kRedBlocks, (long long)m->C, 0);
+// out[0..K) = sum of the `rows` rows of m->part (few columns)
+mlf_status reduce_part(mlf_nop* m, long long rows, int K, float* out) {
+  NLAUNCH(sum_rows_few, dim3((unsigned)((K + kFewCols - 1) / kFewCols)), dim3(kFewCols * kFewGroups), 0, m->stream,
+          m->part, out, (int)rows, K);
   return MLF_OK;
+}
+
+// Weight gradient of a patch layer (with SUMS also its bias gradient, which
+// follows the weights in the parameter vector) into dw.
+template <int NL, bool SUMS>
+mlf_status patch_grad_nl(mlf_nop* m, int batch, const float* img, const float* mean, float scale, const float* lat,
+                         float* dw) {
+  const long long runs = (long long)batch * m->gy * (m->gx / 64);
+  const unsigned blocks = (unsigned)std::min<long long>(kRedBlocks, (runs + 3) / 4);
+  if (m->C == 64)
+    NLAUNCH((patch_outer<NL, 64, SUMS>), dim3(blocks), dim3(256), 0, m->stream, img, mean, scale, lat, m->part,
+            m->p.ny, m->p.nx, runs);
+  else
+    NLAUNCH((patch_outer<NL, 128, SUMS>), dim3(blocks), dim3(256), 0, m->stream, img, mean, scale, lat, m->part,
+            m->p.ny, m->p.nx, runs);
+  return reduce_part(m, blocks, m->J * m->C + (SUMS ? m->J : 0), dw);
+}
+template <bool SUMS>
+mlf_status patch_grad(mlf_nop* m, int batch, const float* img, const float* mean, float scale, const float* lat,
+                      float* dw) {
+  switch (m->p.n_layers) {
+    case 1: return patch_grad_nl<1, SUMS>(m, batch, img, mean, scale, lat, dw);
+    case 2: return patch_grad_nl<2, SUMS>(m, batch, img, mean, scale, lat, dw);
+    case 3: return patch_grad_nl<3, SUMS>(m, batch, img, mean, scale, lat, dw);
+    default: return patch_grad_nl<4, SUMS>(m, batch, img, mean, scale, lat, dw);
+  }
 }
 
 mlf_status refresh_weights(mlf_nop* m) {
@@ -727,26 +745,17 @@ mlf_status refresh_weights(mlf_nop* m) {
   return MLF_OK;
 }
 
-// Forward pass to the increment m->D, keeping the activations for the
-// backward pass.  predict: the encoder forms its input on the fly and the
-// decoder output keeps its plane means (mlf_nop_predict's tail removes them
-// while adding the increment to h); otherwise the encoder input x and the
-// mass-free increment D are kept for the loss and the backward pass.
-mlf_status forward(mlf_nop* m, int batch, const float* h, bool predict) {
+// Forward pass to the decoder output m->D and its plane means m->mean (the
+// increment is their difference, formed by the prediction's tail or by the
+// loss).  `train` keeps the pre-activations for the backward pass.
+mlf_status forward(mlf_nop* m, int batch, const float* h, bool train) {
   const int N = m->p.n_layers;
   const long long plane = (long long)m->p.ny * m->p.nx;
   const long long npix = (long long)batch * m->gy * m->gx, lat = npix * m->C;
-  const dim3 pg = plane_grid(plane, (long long)batch * N);
-  const float inv_s = (float)(1.0 / m->p.scale);
-  NLAUNCH(plane_mean, dim3(batch * N), dim3(1024), 0, m->stream, h, m->mean, plane);
-  if (predict) {
-    NLAUNCH((patch_to_latent<true, true>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, h, m->par + m->oWe,
-            m->par + m->obe, m->r, m->rb, N, m->p.ny, m->p.nx, m->C, batch, m->mean, inv_s);
-  } else {
-    NLAUNCH(center_scale, pg, dim3(256), 0, m->stream, h, m->mean, m->x, plane, inv_s);
-    NLAUNCH((patch_to_latent<true, false>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, m->x, m->par + m->oWe,
-            m->par + m->obe, m->r, m->rb, N, m->p.ny, m->p.nx, m->C, batch, nullptr, 0.f);
-  }
+  NLAUNCH(plane_mean, dim3(batch * N), dim3(1024), 0, m->stream, h, m->mean_h, plane);
+  NLAUNCH((patch_to_latent<false>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, h, m->par + m->oWe,
+          m->par + m->obe, m->r, m->rb, nullptr, N, m->p.ny, m->p.nx, m->C, batch, m->mean_h,
+          (float)(1.0 / m->p.scale));
   const long long cc = 9LL * m->C * m->C;
   for (int l = 0; l < m->L; ++l) {
     float* rl = m->r + l * m->lat;
@@ -755,8 +764,9 @@ mlf_status forward(mlf_nop* m, int batch, const float* h, bool predict) {
     __bf16* glb = m->gb + l * m->lat;
     // a = W1 * r + b1 and its GELU in BF16; r_{l+1} = r + W2 * gelu(a) + b2
     // and its BF16 copy, both in the convolutions' epilogues
-    mlf_status st = conv_fwd_e<nop::kEpiGelu>(m, batch, rlb, m->w1b + l * cc,
-                                              m->par + m->ob1 + l * m->blk_stride, al, nullptr, glb);
+    const float* b1 = m->par + m->ob1 + l * m->blk_stride;
+    mlf_status st = train ? conv_fwd_e<nop::kEpiGelu>(m, batch, rlb, m->w1b + l * cc, b1, al, nullptr, glb)
+                          : conv_fwd_e<nop::kEpiGeluB>(m, batch, rlb, m->w1b + l * cc, b1, nullptr, nullptr, glb);
     if (st != MLF_OK) return st;
     st = conv_fwd_e<nop::kEpiResid>(m, batch, glb, m->w2b + l * cc, m->par + m->ob2 + l * m->blk_stride,
                                     m->r + (l + 1) * m->lat, rl, m->rb + (l + 1) * m->lat);
@@ -765,63 +775,63 @@ mlf_status forward(mlf_nop* m, int batch, const float* h, bool predict) {
   NLAUNCH(dec_fwd, dim3((unsigned)((npix / 64 * N + 3) / 4)), dim3(256), 0, m->stream, m->r + m->L * m->lat,
           m->par + m->oWd, m->par + m->obd, m->D, N, m->p.ny, m->p.nx, m->C, batch);
   NLAUNCH(plane_mean, dim3(batch * N), dim3(1024), 0, m->stream, m->D, m->mean, plane);
-  if (!predict) NLAUNCH(sub_plane_mean, pg, dim3(256), 0, m->stream, m->D, m->mean, plane);
   return MLF_OK;
 }
 
-// loss of the current m->D against the increment target, gradient into m->dD
-mlf_status loss_and_grad(mlf_nop* m, int batch, const float* h0, const float* h1, bool want_grad, double* loss) {
-  const int N = m->p.n_layers;
-  const long long plane = (long long)m->p.ny * m->p.nx, img = (long long)batch * N * plane;
-  NLAUNCH(target_inc, dim3(grid1(img)), dim3(256), 0, m->stream, h0, h1, m->tgt, (float)(1.0 / m->p.scale), img);
-  NLAUNCH(mse, dim3(kRedBlocks), dim3(256), 0, m->stream, m->D, m->tgt, want_grad ? m->dD : nullptr, m->loss_part,
-          img);
-  float parts[kRedBlocks];
-  NHIP(hipMemcpyAsync(parts, m->loss_part, sizeof parts, hipMemcpyDeviceToHost, m->stream));
+// Loss of the current increment against the target into m->loss (times the
+// number of values), with want_grad its gradient into m->dD.
+mlf_status loss_and_grad(mlf_nop* m, int batch, const float* h0, const float* h1, bool want_grad) {
+  const int planes = batch * m->p.n_layers;
+  const long long plane = (long long)m->p.ny * m->p.nx, img = planes * plane;
+  NLAUNCH(loss_grad, dim3(kLossBlocks, planes), dim3(256), 0, m->stream, m->D, m->mean, h0, h1,
+          (float)(1.0 / m->p.scale), 2.f / (float)img, want_grad ? m->dD : nullptr, m->loss_part, plane);
+  NLAUNCH(loss_finish, dim3(1), dim3(256), 0, m->stream, m->loss_part, m->loss, planes * kLossBlocks);
+  return MLF_OK;
+}
+
+// Loss of loss_and_grad on the host (synchronises).
+mlf_status read_loss(mlf_nop* m, int batch, double* loss) {
+  double sum = 0.0;
+  NHIP(hipMemcpyAsync(&sum, m->loss, sizeof sum, hipMemcpyDeviceToHost, m->stream));
   NHIP(hipStreamSynchronize(m->stream));
-  double s = 0.0;
-  for (int i = 0; i < kRedBlocks; ++i) s += parts[i];
-  *loss = s / (double)img;
+  *loss = sum / ((double)batch * m->p.n_layers * m->p.ny * m->p.nx);
   return MLF_OK;
 }
 
 // gradient of the loss w.r.t. all parameters into m->grad (after forward
-// and loss_and_grad with the gradient)
-mlf_status backward(mlf_nop* m, int batch) {
+// from the heights h and loss_and_grad with the gradient)
+mlf_status backward(mlf_nop* m, int batch, const float* h) {
   const int N = m->p.n_layers;
   const long long plane = (long long)m->p.ny * m->p.nx;
-  const long long npix = (long long)batch * m->gy * m->gx, lat = npix * m->C, J = m->J, C = m->C;
-  const long long cc = 9LL * C * C;
-  // the projection (no net mass change) is symmetric: project the gradient
+  const long long npix = (long long)batch * m->gy * m->gx, lat = npix * m->C, rows = npix / 64;
+  const long long cc = 9LL * m->C * m->C;
+  mlf_status st;
+  // the projection (no net mass change) is symmetric: the gradient is
+  // projected where it is read, from its plane means
   NLAUNCH(plane_mean, dim3(batch * N), dim3(1024), 0, m->stream, m->dD, m->mean, plane);
-  NLAUNCH(sub_plane_mean, plane_grid(plane, (long long)batch * N), dim3(256), 0, m->stream, m->dD, m->mean, plane);
-  // decoder: weights, bias, input gradient
-  NLAUNCH(patch_outer, dim3(kRedBlocks), dim3(256), 0, m->stream, m->dD, m->r + m->L * m->lat, m->part, N, m->p.ny,
-          m->p.nx, m->C, npix);
-  NLAUNCH(sum_rows, dim3(grid1(J * C)), dim3(256), 0, m->stream, m->part, m->grad + m->oWd, kRedBlocks, J * C, 0);
-  NLAUNCH(patch_sum, dim3(kRedBlocks), dim3(256), 0, m->stream, m->dD, m->part, N, m->p.ny, m->p.nx, npix);
-  NLAUNCH(sum_rows, dim3(grid1(J)), dim3(256), 0, m->stream, m->part, m->grad + m->obd, kRedBlocks, J, 0);
-  NLAUNCH((patch_to_latent<false, false>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, m->dD, m->par + m->oWd,
-          nullptr, m->dr, nullptr, N, m->p.ny, m->p.nx, m->C, batch, nullptr, 0.f);
-  // residual blocks, last to first; m->dr holds dL/dr_{l+1}
+  // decoder: weights and bias, input gradient
+  if ((st = patch_grad<true>(m, batch, m->dD, m->mean, 1.f, m->r + m->L * m->lat, m->grad + m->oWd)) != MLF_OK)
+    return st;
+  NLAUNCH((patch_to_latent<true>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, m->dD, m->par + m->oWd, nullptr,
+          m->dr, m->cb, m->part, N, m->p.ny, m->p.nx, m->C, batch, m->mean, 1.f);
+  // residual blocks, last to first; m->dr (and its BF16 copy m->cb) hold
+  // dL/dr_{l+1}, m->part its column sums
   for (int l = m->L - 1; l >= 0; --l) {
     const long long ob = l * m->blk_stride;
-    mlf_status st;
-    NLAUNCH(to_bf16, dim3(grid1(lat)), dim3(256), 0, m->stream, m->dr, m->cb, lat);
-    if ((st = bias_grad(m, npix, m->dr, m->grad + m->ob2 + ob)) != MLF_OK) return st;
+    if ((st = reduce_part(m, rows, m->C, m->grad + m->ob2 + ob)) != MLF_OK) return st;
     if ((st = conv_wgrad(m, batch, m->gb + l * m->lat, m->cb, m->grad + m->oW2 + ob)) != MLF_OK) return st;
-    if ((st = conv_fwd(m, batch, m->cb, m->w2t + l * cc, nullptr, m->tmp)) != MLF_OK) return st;
-    NLAUNCH(gelu_bwd, dim3(grid1(lat)), dim3(256), 0, m->stream, m->tmp, m->a + l * m->lat, m->c, m->cb, lat);
-    if ((st = bias_grad(m, npix, m->c, m->grad + m->ob1 + ob)) != MLF_OK) return st;
-    if ((st = conv_wgrad(m, batch, m->rb + l * m->lat, m->cb, m->grad + m->oW1 + ob)) != MLF_OK) return st;
-    if ((st = conv_fwd(m, batch, m->cb, m->w1t + l * cc, nullptr, m->tmp)) != MLF_OK) return st;
-    NLAUNCH(add_into, dim3(grid1(lat)), dim3(256), 0, m->stream, m->dr, m->tmp, nullptr, lat);
+    if ((st = conv_fwd_e<nop::kEpiGrad>(m, batch, m->cb, m->w2t + l * cc, nullptr, nullptr, m->a + l * m->lat, m->cb2,
+                                        m->part)) != MLF_OK)
+      return st;
+    if ((st = reduce_part(m, rows, m->C, m->grad + m->ob1 + ob)) != MLF_OK) return st;
+    if ((st = conv_wgrad(m, batch, m->rb + l * m->lat, m->cb2, m->grad + m->oW1 + ob)) != MLF_OK) return st;
+    if ((st = conv_fwd_e<nop::kEpiAcc>(m, batch, m->cb2, m->w1t + l * cc, nullptr, m->dr, m->dr,
+                                       l > 0 ? m->cb : nullptr, m->part)) != MLF_OK)
+      return st;
   }
   // encoder
-  NLAUNCH(patch_outer, dim3(kRedBlocks), dim3(256), 0, m->stream, m->x, m->dr, m->part, N, m->p.ny, m->p.nx, m->C,
-          npix);
-  NLAUNCH(sum_rows, dim3(grid1(J * C)), dim3(256), 0, m->stream, m->part, m->grad + m->oWe, kRedBlocks, J * C, 0);
-  return bias_grad(m, npix, m->dr, m->grad + m->obe);
+  if ((st = reduce_part(m, rows, m->C, m->grad + m->obe)) != MLF_OK) return st;
+  return patch_grad<false>(m, batch, h, m->mean_h, (float)(1.0 / m->p.scale), m->dr, m->grad + m->oWe);
 }
 
 mlf_status check_batch(mlf_nop* m, int batch) {
@@ -874,21 +884,20 @@ mlf_status mlf_nop_create(const mlf_nop_params* p, void* workspace, void* stream
   m->w1t = wb + cc;
   m->w2b = wb + 2 * cc;
   m->w2t = wb + 3 * cc;
-  m->x = reinterpret_cast<float*>(w + s.off[5]);
-  m->tgt = reinterpret_cast<float*>(w + s.off[6]);
-  m->D = reinterpret_cast<float*>(w + s.off[7]);
-  m->dD = reinterpret_cast<float*>(w + s.off[8]);
-  m->mean = reinterpret_cast<float*>(w + s.off[9]);
-  m->loss_part = reinterpret_cast<float*>(w + s.off[10]);
+  m->D = reinterpret_cast<float*>(w + s.off[5]);
+  m->dD = reinterpret_cast<float*>(w + s.off[6]);
+  m->mean = reinterpret_cast<float*>(w + s.off[7]);
+  m->mean_h = reinterpret_cast<float*>(w + s.off[8]);
+  m->loss_part = reinterpret_cast<float*>(w + s.off[9]);
+  m->loss = reinterpret_cast<double*>(w + s.off[10]);
   m->r = reinterpret_cast<float*>(w + s.off[11]);
   m->a = reinterpret_cast<float*>(w + s.off[12]);
-  m->c = reinterpret_cast<float*>(w + s.off[13]);
-  m->dr = reinterpret_cast<float*>(w + s.off[14]);
-  m->tmp = reinterpret_cast<float*>(w + s.off[15]);
-  m->rb = reinterpret_cast<__bf16*>(w + s.off[16]);
-  m->gb = reinterpret_cast<__bf16*>(w + s.off[17]);
-  m->cb = reinterpret_cast<__bf16*>(w + s.off[18]);
-  m->part = reinterpret_cast<float*>(w + s.off[19]);
+  m->dr = reinterpret_cast<float*>(w + s.off[13]);
+  m->rb = reinterpret_cast<__bf16*>(w + s.off[14]);
+  m->gb = reinterpret_cast<__bf16*>(w + s.off[15]);
+  m->cb = reinterpret_cast<__bf16*>(w + s.off[16]);
+  m->cb2 = reinterpret_cast<__bf16*>(w + s.off[17]);
+  m->part = reinterpret_cast<float*>(w + s.off[18]);
   m->adam_t = 0;
   if ((st = set_lds_limits(m)) != MLF_OK) {
     delete m;
@@ -922,7 +931,7 @@ mlf_status mlf_nop_predict(mlf_nop* m, int32_t batch, const float* h, float* out
   if (!m || !h || !out) return MLF_EINVAL;
   mlf_status st = check_batch(m, batch);
   if (st != MLF_OK) return st;
-  if ((st = forward(m, batch, h, true)) != MLF_OK) return st;
+  if ((st = forward(m, batch, h, false)) != MLF_OK) return st;
   const long long plane = (long long)m->p.ny * m->p.nx;
   NLAUNCH(sub_mean_axpy, plane_grid(plane, (long long)batch * m->p.n_layers), dim3(256), 0, m->stream, h, m->D,
           m->mean, out, (float)m->p.scale, plane);
@@ -934,7 +943,8 @@ mlf_status mlf_nop_loss(mlf_nop* m, int32_t batch, const float* h0, const float*
   mlf_status st = check_batch(m, batch);
   if (st != MLF_OK) return st;
   if ((st = forward(m, batch, h0, false)) != MLF_OK) return st;
-  return loss_and_grad(m, batch, h0, h1, false, loss);
+  if ((st = loss_and_grad(m, batch, h0, h1, false)) != MLF_OK) return st;
+  return read_loss(m, batch, loss);
 }
 
 mlf_status mlf_nop_gradient(mlf_nop* m, int32_t batch, const float* h0, const float* h1, float* host_grad,
@@ -942,9 +952,10 @@ mlf_status mlf_nop_gradient(mlf_nop* m, int32_t batch, const float* h0, const fl
   if (!m || !h0 || !h1 || !loss) return MLF_EINVAL;
   mlf_status st = check_batch(m, batch);
   if (st != MLF_OK) return st;
-  if ((st = forward(m, batch, h0, false)) != MLF_OK) return st;
-  if ((st = loss_and_grad(m, batch, h0, h1, true, loss)) != MLF_OK) return st;
-  if ((st = backward(m, batch)) != MLF_OK) return st;
+  if ((st = forward(m, batch, h0, true)) != MLF_OK) return st;
+  if ((st = loss_and_grad(m, batch, h0, h1, true)) != MLF_OK) return st;
+  if ((st = backward(m, batch, h0)) != MLF_OK) return st;
+  if ((st = read_loss(m, batch, loss)) != MLF_OK) return st;  // after everything is enqueued
   if (host_grad) {
     NHIP(hipMemcpyAsync(host_grad, m->grad, (size_t)m->npar * sizeof(float), hipMemcpyDeviceToHost, m->stream));
     NHIP(hipStreamSynchronize(m->stream));
