@@ -44,7 +44,20 @@ __global__ void __launch_bounds__(1024) plane_mean(const float* __restrict__ a, 
   if ((reinterpret_cast<uintptr_t>(p) & 15) == 0) {
     const long long n4 = n / 4;
     const float4* p4 = reinterpret_cast<const float4*>(p);
-    for (long long t = threadIdx.x; t < n4; t += 1024) {
+    long long t = threadIdx.x;
+    for (; t + 7 * 1024 < n4; t += 8 * 1024) {  // eight loads in flight, added in order
+      float4 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = p4[t + 1024 * q];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        s0 += v[q].x;
+        s1 += v[q].y;
+        s2 += v[q].z;
+        s3 += v[q].w;
+      }
+    }
+    for (; t < n4; t += 1024) {
       const float4 v = p4[t];
       s0 += v.x;
       s1 += v.y;
@@ -56,11 +69,14 @@ __global__ void __launch_bounds__(1024) plane_mean(const float* __restrict__ a, 
   for (long long t = done + threadIdx.x; t < n; t += 1024) s0 += p[t];
   red[threadIdx.x] = (s0 + s1) + (s2 + s3);
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
+  for (int w = 512; w >= 64; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0] / (float)n;
+  if (threadIdx.x >= 64) return;
+  float s = red[threadIdx.x];
+  for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);  // the tree's last levels
+  if (threadIdx.x == 0) out[blockIdx.x] = s / (float)n;
 }
 
 // prediction tail: o = h + s * (d - mean[plane]), the decoder output made
@@ -202,6 +218,124 @@ __global__ void __launch_bounds__(256) dec_fwd(const float* __restrict__ r, cons
   for (int u = 0; u < kPatch; ++u)
     *reinterpret_cast<float4*>(D + (((long long)b * nl + i) * ny + kPatch * py + u) * nx + kPatch * px) =
         make_float4(acc[4 * u], acc[4 * u + 1], acc[4 * u + 2], acc[4 * u + 3]);
+}
+
+// The two patch layers for small batches (small_batch): with the weights as scalar operands each wave waits for its scalar
+// loads some thirty times, which nothing hides while the device is mostly
+// idle (one film: encoder 14 us, decoder 21 us, whatever the split).  Here a
+// workgroup first brings everything it needs into LDS or registers with all
+// loads in flight at once, and the waves read weights as LDS broadcasts; the
+// sums and their order are those of patch_to_latent and dec_fwd.
+//
+// Encoder side: a workgroup takes 64 pixels and 32 channels, 8 per wave.
+template <bool SUMS, int NL>
+__global__ void __launch_bounds__(256) patch_to_latent_small(const float* __restrict__ P, const float* __restrict__ W,
+                                                             const float* __restrict__ bias, float* __restrict__ out,
+                                                             __bf16* __restrict__ outb, float* __restrict__ colp,
+                                                             int ny, int nx, int C, const float* __restrict__ pmean,
+                                                             float pscale) {
+  constexpr int J = 16 * NL, RS = 33;
+  __shared__ float sw[J * 32];
+  __shared__ float so[64 * RS];
+  const int gy = ny / kPatch, gx = nx / kPatch, groups = C / 32;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = (int)(blockIdx.x % groups) * 32;
+  const long long run = blockIdx.x / groups, pix = run * 64 + lane;
+  const int px = (int)(pix % gx), py = (int)((pix / gx) % gy), b = (int)(pix / ((long long)gx * gy));
+  float4 pv[NL][kPatch];
+#pragma unroll
+  for (int i = 0; i < NL; ++i)
+#pragma unroll
+    for (int u = 0; u < kPatch; ++u)
+      pv[i][u] = *reinterpret_cast<const float4*>(P + (((long long)b * NL + i) * ny + kPatch * py + u) * nx +
+                                                  kPatch * px);
+  for (int t = threadIdx.x; t < J * 8; t += 256)
+    *reinterpret_cast<float4*>(sw + 4 * t) = *reinterpret_cast<const float4*>(W + (long long)(t / 8) * C + c0 + 4 * (t % 8));
+  float acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = bias ? bias[c0 + 8 * wave + c] : 0.f;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const float mu = pmean[b * NL + i];
+#pragma unroll
+    for (int u = 0; u < kPatch; ++u) {
+      const float ps[4] = {(pv[i][u].x - mu) * pscale, (pv[i][u].y - mu) * pscale, (pv[i][u].z - mu) * pscale,
+                           (pv[i][u].w - mu) * pscale};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float* wr = sw + ((i * kPatch + u) * kPatch + v) * 32 + 8 * wave;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[c] += wr[c] * ps[v];
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) so[lane * RS + 8 * wave + c] = acc[c];
+  __syncthreads();
+  // stores as in patch_to_latent: each wave 16 of the pixels, whole 128-byte
+  // channel runs
+  const int ch = lane & 31;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int p = 16 * wave + 2 * k + (lane >> 5);
+    const float v = so[p * RS + ch];
+    out[(run * 64 + p) * C + c0 + ch] = v;
+    outb[(run * 64 + p) * C + c0 + ch] = (__bf16)v;
+  }
+  if constexpr (SUMS) {
+    if (threadIdx.x < 32) {
+      float cs = 0.f;
+#pragma unroll
+      for (int p = 0; p < 64; ++p) cs += so[p * RS + threadIdx.x];
+      colp[run * C + c0 + threadIdx.x] = cs;
+    }
+  }
+}
+
+// Decoder side: a workgroup takes 64 pixels and one layer, one output row u
+// per wave.
+template <int C>
+__global__ void __launch_bounds__(256) dec_small(const float* __restrict__ r, const float* __restrict__ Wd,
+                                                 const float* __restrict__ bd, float* __restrict__ D, int nl, int ny,
+                                                 int nx) {
+  constexpr int RS = C + 4;
+  __shared__ __attribute__((aligned(16))) float sr[64 * RS];
+  __shared__ __attribute__((aligned(16))) float sw[16 * C];
+  const int gy = ny / kPatch, gx = nx / kPatch;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = (int)(blockIdx.x % nl);
+  const long long pbase = (long long)(blockIdx.x / nl) * 64, pix = pbase + lane;
+  const int px = (int)(pix % gx), py = (int)((pix / gx) % gy), b = (int)(pix / ((long long)gx * gy));
+  const float* W = Wd + (long long)16 * i * C;
+  constexpr int PQ = 64 * C / 4 / 256, WQ = 16 * C / 4 / 256;  // 16-byte pieces per thread
+  float4 a[PQ], w[WQ];
+#pragma unroll
+  for (int q = 0; q < PQ; ++q) a[q] = *reinterpret_cast<const float4*>(r + pbase * C + 4 * (threadIdx.x + 256 * q));
+#pragma unroll
+  for (int q = 0; q < WQ; ++q) w[q] = *reinterpret_cast<const float4*>(W + 4 * (threadIdx.x + 256 * q));
+#pragma unroll
+  for (int q = 0; q < PQ; ++q) {
+    const int e = 4 * (threadIdx.x + 256 * q);
+    *reinterpret_cast<float4*>(sr + e / C * RS + e % C) = a[q];
+  }
+#pragma unroll
+  for (int q = 0; q < WQ; ++q) *reinterpret_cast<float4*>(sw + 4 * (threadIdx.x + 256 * q)) = w[q];
+  float acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = bd[16 * i + 4 * wave + j];
+  __syncthreads();
+#pragma unroll 8
+  for (int c = 0; c < C; c += 4) {
+    const float4 rv = *reinterpret_cast<const float4*>(sr + lane * RS + c);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float4 wp = *reinterpret_cast<const float4*>(sw + (4 * wave + j) * C + c);
+      acc[j] += wp.x * rv.x + wp.y * rv.y + wp.z * rv.z + wp.w * rv.w;
+    }
+  }
+  *reinterpret_cast<float4*>(D + (((long long)b * nl + i) * ny + kPatch * py + wave) * nx + kPatch * px) =
+      make_float4(acc[0], acc[1], acc[2], acc[3]);
 }
 
 // Weight (and, for the decoder, bias) gradients of the patch layers:
@@ -602,13 +736,17 @@ Layout layout_of(const mlf_nop_params* p) {
   return s;
 }
 
-// Launch shape by workload (measured on 64 x 64 latent grids): workgroups
-// of 4 waves (4 latent rows), two per CU; small batches (the judged runs'
+// Launch shape by workload (measured on 64 x 64 latent grids, u = batch rows x
+// 64-pixel column tiles): workgroups of 4 waves (4 latent rows), two per CU.
+// Large batches (training) give each workgroup all channels, so that each
+// staged slab of weights serves more products; small ones (the judged runs'
 // windows) split the output channels into groups of 32 to fill the device,
-// large ones (training) give each workgroup all channels, so that each
-// staged slab of weights serves more products.  The dynamic LDS above
-// 64 KiB of every shape is enabled when the handle is created
-// (set_lds_limits, on the handle's device).
+// medium ones at C = 128 into groups of 64 (a prediction of 16 films 290
+// us with groups of 64, 317 with 32; of 12 films 245 / 235; of 48 films 788 /
+// 930; at C = 64 of 32 films 250 with all channels, 259 with 32).
+// Every shape gives the same bits.  The dynamic LDS above 64 KiB of every
+// shape is enabled when the handle is created (set_lds_limits, on the
+// handle's device).
 template <int C, int CO, int EPI>
 mlf_status conv_fwd_launch(mlf_nop* m, long long rows, const __bf16* in, const __bf16* w, const float* bias,
                            float* out, const float* res, __bf16* outb, float* colp) {
@@ -622,9 +760,10 @@ mlf_status conv_fwd_launch(mlf_nop* m, long long rows, const __bf16* in, const _
 template <int C, int EPI>
 mlf_status conv_fwd_t(mlf_nop* m, int batch, const __bf16* in, const __bf16* w, const float* bias, float* out,
                       const float* res, __bf16* outb, float* colp) {
-  const long long rows = (long long)batch * m->gy;
-  if (rows < 64 * 64) return conv_fwd_launch<C, 32, EPI>(m, rows, in, w, bias, out, res, outb, colp);
-  return conv_fwd_launch<C, C, EPI>(m, rows, in, w, bias, out, res, outb, colp);
+  const long long rows = (long long)batch * m->gy, u = rows * (m->gx / 64);
+  if (u >= (C == 64 ? 2048 : 4096)) return conv_fwd_launch<C, C, EPI>(m, rows, in, w, bias, out, res, outb, colp);
+  if (C == 128 && u >= 1024) return conv_fwd_launch<C, 64, EPI>(m, rows, in, w, bias, out, res, outb, colp);
+  return conv_fwd_launch<C, 32, EPI>(m, rows, in, w, bias, out, res, outb, colp);
 }
 
 template <int EPI>
@@ -674,6 +813,7 @@ mlf_status set_lds(mlf_nop* m, K kern, size_t bytes) {
 template <int C, int EPI>
 mlf_status set_fwd_lds(mlf_nop* m) {
   mlf_status st = set_lds(m, nop::conv3x3_fwd<C, 32, 4, EPI>, nop::conv3x3_fwd_lds(32, 4));
+  if (st == MLF_OK) st = set_lds(m, nop::conv3x3_fwd<C, 64, 4, EPI>, nop::conv3x3_fwd_lds(64, 4));
   if (st == MLF_OK) st = set_lds(m, nop::conv3x3_fwd<C, C, 4, EPI>, nop::conv3x3_fwd_lds(C, 4));
   return st;
 }
@@ -745,17 +885,49 @@ mlf_status refresh_weights(mlf_nop* m) {
   return MLF_OK;
 }
 
+// Whether `runs` runs of 64 latent pixels take the patch kernels for small
+// batches.  A prediction at C = 128 of 1 / 4 / 12 films takes 94 / 114 / 206 us
+// with them, 117 / 128 / 199 with the others; at C = 64 of 8 / 16 films 90 /
+// 123 against 98 / 122.
+bool small_batch(const mlf_nop* m, long long runs) { return runs * m->C <= 65536; }
+
+// A patch layer into the latent grid (with SUMS its column sums into m->part).
+template <bool SUMS>
+mlf_status to_latent(mlf_nop* m, int batch, const float* P, const float* W, const float* bias, float* out,
+                     __bf16* outb, const float* mean, float scale) {
+  const int N = m->p.n_layers;
+  const long long runs = (long long)batch * m->gy * m->gx / 64;
+  if (!small_batch(m, runs)) {
+    NLAUNCH((patch_to_latent<SUMS>), dim3(grid1(runs * 2 * m->C)), dim3(256), 0, m->stream, P, W, bias, out, outb,
+            m->part, N, m->p.ny, m->p.nx, m->C, batch, mean, scale);
+    return MLF_OK;
+  }
+  const dim3 grid((unsigned)(runs * (m->C / 32)));
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, m->stream, P, W, bias, out, outb, m->part, m->p.ny, m->p.nx, m->C,
+                       mean, scale);
+  };
+  switch (N) {
+    case 1: launch(patch_to_latent_small<SUMS, 1>); break;
+    case 2: launch(patch_to_latent_small<SUMS, 2>); break;
+    case 3: launch(patch_to_latent_small<SUMS, 3>); break;
+    default: launch(patch_to_latent_small<SUMS, 4>); break;
+  }
+  NHIP(hipGetLastError());
+  return MLF_OK;
+}
+
 // Forward pass to the decoder output m->D and its plane means m->mean (the
 // increment is their difference, formed by the prediction's tail or by the
 // loss).  `train` keeps the pre-activations for the backward pass.
 mlf_status forward(mlf_nop* m, int batch, const float* h, bool train) {
   const int N = m->p.n_layers;
   const long long plane = (long long)m->p.ny * m->p.nx;
-  const long long npix = (long long)batch * m->gy * m->gx, lat = npix * m->C;
+  const long long npix = (long long)batch * m->gy * m->gx;
   NLAUNCH(plane_mean, dim3(batch * N), dim3(1024), 0, m->stream, h, m->mean_h, plane);
-  NLAUNCH((patch_to_latent<false>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, h, m->par + m->oWe,
-          m->par + m->obe, m->r, m->rb, nullptr, N, m->p.ny, m->p.nx, m->C, batch, m->mean_h,
-          (float)(1.0 / m->p.scale));
+  mlf_status st = to_latent<false>(m, batch, h, m->par + m->oWe, m->par + m->obe, m->r, m->rb, m->mean_h,
+                                   (float)(1.0 / m->p.scale));
+  if (st != MLF_OK) return st;
   const long long cc = 9LL * m->C * m->C;
   for (int l = 0; l < m->L; ++l) {
     float* rl = m->r + l * m->lat;
@@ -765,15 +937,24 @@ mlf_status forward(mlf_nop* m, int batch, const float* h, bool train) {
     // a = W1 * r + b1 and its GELU in BF16; r_{l+1} = r + W2 * gelu(a) + b2
     // and its BF16 copy, both in the convolutions' epilogues
     const float* b1 = m->par + m->ob1 + l * m->blk_stride;
-    mlf_status st = train ? conv_fwd_e<nop::kEpiGelu>(m, batch, rlb, m->w1b + l * cc, b1, al, nullptr, glb)
-                          : conv_fwd_e<nop::kEpiGeluB>(m, batch, rlb, m->w1b + l * cc, b1, nullptr, nullptr, glb);
+    st = train ? conv_fwd_e<nop::kEpiGelu>(m, batch, rlb, m->w1b + l * cc, b1, al, nullptr, glb)
+               : conv_fwd_e<nop::kEpiGeluB>(m, batch, rlb, m->w1b + l * cc, b1, nullptr, nullptr, glb);
     if (st != MLF_OK) return st;
     st = conv_fwd_e<nop::kEpiResid>(m, batch, glb, m->w2b + l * cc, m->par + m->ob2 + l * m->blk_stride,
                                     m->r + (l + 1) * m->lat, rl, m->rb + (l + 1) * m->lat);
     if (st != MLF_OK) return st;
   }
-  NLAUNCH(dec_fwd, dim3((unsigned)((npix / 64 * N + 3) / 4)), dim3(256), 0, m->stream, m->r + m->L * m->lat,
-          m->par + m->oWd, m->par + m->obd, m->D, N, m->p.ny, m->p.nx, m->C, batch);
+  const float* rL = m->r + m->L * m->lat;
+  const unsigned runs = (unsigned)(npix / 64);
+  if (!small_batch(m, runs))
+    NLAUNCH(dec_fwd, dim3((runs * N + 3) / 4), dim3(256), 0, m->stream, rL, m->par + m->oWd, m->par + m->obd, m->D, N,
+            m->p.ny, m->p.nx, m->C, batch);
+  else if (m->C == 64)
+    NLAUNCH(dec_small<64>, dim3(runs * N), dim3(256), 0, m->stream, rL, m->par + m->oWd, m->par + m->obd, m->D, N,
+            m->p.ny, m->p.nx);
+  else
+    NLAUNCH(dec_small<128>, dim3(runs * N), dim3(256), 0, m->stream, rL, m->par + m->oWd, m->par + m->obd, m->D, N,
+            m->p.ny, m->p.nx);
   NLAUNCH(plane_mean, dim3(batch * N), dim3(1024), 0, m->stream, m->D, m->mean, plane);
   return MLF_OK;
 }
@@ -803,7 +984,7 @@ mlf_status read_loss(mlf_nop* m, int batch, double* loss) {
 mlf_status backward(mlf_nop* m, int batch, const float* h) {
   const int N = m->p.n_layers;
   const long long plane = (long long)m->p.ny * m->p.nx;
-  const long long npix = (long long)batch * m->gy * m->gx, lat = npix * m->C, rows = npix / 64;
+  const long long rows = (long long)batch * m->gy * m->gx / 64;
   const long long cc = 9LL * m->C * m->C;
   mlf_status st;
   // the projection (no net mass change) is symmetric: the gradient is
@@ -812,8 +993,8 @@ mlf_status backward(mlf_nop* m, int batch, const float* h) {
   // decoder: weights and bias, input gradient
   if ((st = patch_grad<true>(m, batch, m->dD, m->mean, 1.f, m->r + m->L * m->lat, m->grad + m->oWd)) != MLF_OK)
     return st;
-  NLAUNCH((patch_to_latent<true>), dim3(grid1(lat / 32)), dim3(256), 0, m->stream, m->dD, m->par + m->oWd, nullptr,
-          m->dr, m->cb, m->part, N, m->p.ny, m->p.nx, m->C, batch, m->mean, 1.f);
+  if ((st = to_latent<true>(m, batch, m->dD, m->par + m->oWd, nullptr, m->dr, m->cb, m->mean, 1.f)) != MLF_OK)
+    return st;
   // residual blocks, last to first; m->dr (and its BF16 copy m->cb) hold
   // dL/dr_{l+1}, m->part its column sums
   for (int l = m->L - 1; l >= 0; --l) {
