@@ -1079,8 +1079,9 @@ struct RowPipe {
 // Lane l holds column x0 - HALO + l; x neighbours come from the neighbouring
 // lanes, rows are marched in +y, and nothing is shared between wavefronts.
 // `sr_step` is the film's step count, the counter of its stochastic-rounding
-// draws (read only when kc.sr_on; one step only).
-template <typename R, typename S, typename C, int NL, bool TAU1, int EA, int EB, int STEPS>
+// draws (read only when kc.sr_on; one step only).  AHEAD loads a row while the
+// one before it is processed.
+template <typename R, typename S, typename C, int NL, bool TAU1, int EA, int EB, int STEPS, bool AHEAD>
 __device__ inline void march_tile(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
                                   const StepConsts<C>& kc, int tile, uint32_t sr_step, C* wave_lds) {
   static_assert(STEPS == 1 || (STEPS == 2 && TAU1), "two steps need tau = 1");
@@ -1178,7 +1179,7 @@ __device__ inline void march_tile(const unsigned char* __restrict__ src, unsigne
   int yl = wrap(y0 - HALO, kc.ny);       // row being loaded
   int ys = wrap(y0 - 2 * HALO, kc.ny);   // row being stored (valid from iteration 2 HALO on)
   auto next_row = [&](int y) { return y + 1 == kc.ny ? 0 : y + 1; };
-  load_row(yl, w0, wk);
+  if constexpr (AHEAD) load_row(yl, w0, wk);
   // Every iteration issues the same vector-memory sequence (the next row's
   // loads, then this row's stores; lanes and rows without output store out
   // of range, which the hardware drops): the compiler's wait for a row's
@@ -1187,6 +1188,7 @@ __device__ inline void march_tile(const unsigned char* __restrict__ src, unsigne
     constexpr int P = decltype(parity)::value;
     const bool live = it < niter;  // false in the last pass of an odd count
     C dh[NL], qx[NL], qy[NL];
+    if constexpr (!AHEAD) load_row(yl, w0, wk);
     {
       C f0[NL], f[kQ - 1][NL];
       unpack<R, NL>(w0, f0);
@@ -1205,7 +1207,7 @@ __device__ inline void march_tile(const unsigned char* __restrict__ src, unsigne
     }
     guard_row<C, NL>(kc, dh, qx, qy, true, low, inf);
     if (it + 1 < niter) yl = next_row(yl);
-    load_row(yl, w0, wk);
+    if constexpr (AHEAD) load_row(yl, w0, wk);
     __builtin_amdgcn_sched_barrier(0);
     // collisions of rows that no output needs are skipped (uniform branches
     // without vector-memory instructions): the first four rows of a step
@@ -1311,12 +1313,16 @@ constexpr int step_max_lanes() {
 template <typename R, typename S, typename C, int NL, bool TAU1, int EA, int EB, int STEPS>
 __global__ void __launch_bounds__((step_max_lanes<C, NL>()))
 step_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst, const StepConsts<C> kc) {
+  // FP64 with three layers: the 54 registers of a row ahead would spill, and
+  // the second wavefront of a SIMD hides its loads (777 x 515 38.7 us per
+  // step, 43.5 with a row ahead)
+  constexpr bool kAhead = !(sizeof(C) == 8 && NL == 3);
   const int group = tile_of_block(blockIdx.x, gridDim.x);
   const int nw = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (group * nw >= kc.nstrip * kc.nseg) return;  // padding workgroup (uniform)
   extern __shared__ unsigned char smem_raw[];
   C* lds = reinterpret_cast<C*>(smem_raw + wave * march_lds<C>(NL, STEPS));
-  march_tile<R, S, C, NL, TAU1, EA, EB, STEPS>(src, dst, kc, group * nw + wave, kc.sr_step, lds);
+  march_tile<R, S, C, NL, TAU1, EA, EB, STEPS, kAhead>(src, dst, kc, group * nw + wave, kc.sr_step, lds);
 }
 
 // The same for a film one row high (FP64 or FP32 storage).
@@ -1348,7 +1354,7 @@ __device__ inline void batch_tile(const unsigned char* __restrict__ src, unsigne
       return;
     }
   }
-  march_tile<R, S, C, NL, TAU1, EA, EB, STEPS>(src, dst, kc, tile, step, lds);
+  march_tile<R, S, C, NL, TAU1, EA, EB, STEPS, true>(src, dst, kc, tile, step, lds);
 }
 
 // One launch advances every film of a batch by STEPS steps.  Work item w
