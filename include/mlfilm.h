@@ -359,8 +359,8 @@ mlf_status mlf_batch_step_until(mlf_batch* b, int64_t max_steps, int32_t check_e
 /* Launch shape shared by all films: block_w in {64, 128, 192, 256}, seg_h
  * >= 1 rows (clamped to each film's ny), persistent != 0: as many
  * workgroups as fit the device at once, each taking work items in turn;
- * 0: one workgroup per item.  0 for block_w selects 256, for seg_h a height
- * by the films' sizes.
+ * 0: one workgroup per item.  0 for block_w or seg_h selects a default by
+ * the films' sizes.
  * EINVAL if the work list would exceed its scratch area. */
 mlf_status mlf_batch_set_launch(mlf_batch* b, int32_t block_w, int32_t seg_h, int32_t persistent);
 mlf_status mlf_batch_get_launch(const mlf_batch* b, int32_t* block_w, int32_t* seg_h, int32_t* persistent);

@@ -2007,8 +2007,13 @@ long long batch_items(const mlf_batch* b, int bw, int sh) {
   return t;
 }
 
-// Default segment height of a batch: the films' tiles together fill the
-// device as one film's do.
+// Default launch shape of a batch: one tile per workgroup (films of uneven
+// sizes and layer counts give uneven tiles, which the device then deals out
+// one by one: 35 films, FP32, 36 rows, 115 us per step, 181 with four), and
+// segments with which the films' tiles together fill the device as one
+// film's do.  FP64 tiles are long (one wavefront per SIMD), so theirs stay at
+// 32 rows or less: 35 films 395 us per step with the read-out, 624 with 68
+// rows and four tiles per workgroup.
 int batch_default_seg(const mlf_batch* b) {
   int ny = 1;
   for (const mlf_handle* h : b->film) ny = std::max(ny, h->p.ny);
@@ -2017,7 +2022,8 @@ int batch_default_seg(const mlf_batch* b) {
     for (const mlf_handle* h : b->film) t += film_tiles(h->p, s);
     return t;
   };
-  return seg_for(tiles, ny, fusable(b->p0));
+  const int sh = seg_for(tiles, ny, fusable(b->p0));
+  return b->p0.precision == MLF_F64 ? std::min(sh, 32) : sh;
 }
 
 // Whether a launch shape is accepted: its tiles, counted as one per bw - 4
@@ -2033,6 +2039,9 @@ bool batch_shape_ok(const mlf_batch* b, int bw, int sh) {
   }
   return t <= kMaxTileUnits;
 }
+
+// The widest workgroup where the work list has no room for one tile each.
+int batch_default_w(const mlf_batch* b, int sh) { return batch_shape_ok(b, 64, sh) ? 64 : 256; }
 
 // Device table and work list for the current launch shape (synchronous).
 template <typename C>
@@ -2050,10 +2059,20 @@ mlf_status upload_table_t(mlf_batch* b) {
     tab[f].offset = (long long)b->offset[f];
     tab[f].nl = h->p.n_layers;
   }
+  // longest items first (layers x rows marched; the last segment of a film may
+  // be short), so that the end of a launch is made of short ones
+  std::vector<std::pair<int, int2>> cost;
+  const int nw = b->block_w / 64, halo = 2 * mlf::march_halo(strip_steps(b->p0));
   for (int f : b->order) {
+    const mlf::StepConsts<C>& k = tab[f].kc;
     const int nt = (int)film_tiles(b, f, b->block_w, b->seg_h);
-    for (int t = 0; t < nt; ++t) items.push_back(make_int2(f, t));
+    for (int t = 0; t < nt; ++t) {
+      const int seg = t * nw / k.nstrip;
+      cost.emplace_back(tab[f].nl * (std::min(k.seg_h, k.ny - seg * k.seg_h) + halo), make_int2(f, t));
+    }
   }
+  std::stable_sort(cost.begin(), cost.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  for (const auto& c : cost) items.push_back(c.second);
   BHIPCHK(hipMemcpyAsync(b->scratch + kBatchTableOff, tab.data(), tab.size() * sizeof(tab[0]),
                          hipMemcpyHostToDevice, b->stream));
   BHIPCHK(hipMemcpyAsync(b->scratch + kBatchItemOff, items.data(), items.size() * sizeof(int2),
@@ -2240,8 +2259,8 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
     auto lu = [&](int f) { return (long long)films[f].n_layers * films[f].nx * films[f].ny; };
     return lu(a) > lu(c);
   });
-  b->block_w = 256;
   b->seg_h = batch_default_seg(b);
+  b->block_w = batch_default_w(b, b->seg_h);
   b->persistent = 0;
   b->ahead = 1;
   if (!batch_shape_ok(b, 256, 8) ||
@@ -2541,11 +2560,11 @@ mlf_status mlf_batch_step_until(mlf_batch* b, int64_t max_steps, int32_t check_e
 
 mlf_status mlf_batch_set_launch(mlf_batch* b, int32_t block_w, int32_t seg_h, int32_t persistent) {
   if (!b) return MLF_EINVAL;
-  const int bw = block_w == 0 ? 256 : block_w, sh = seg_h == 0 ? batch_default_seg(b) : seg_h;
+  const int sh = seg_h == 0 ? batch_default_seg(b) : seg_h, bw = block_w == 0 ? batch_default_w(b, sh) : block_w;
   if (bw != 64 && bw != 128 && bw != 192 && bw != 256)
     return bfail(b, MLF_EINVAL, "block_w must be 64, 128, 192 or 256");
   if (sh < 1) return bfail(b, MLF_EINVAL, "seg_h must be >= 1");
-  if (!batch_shape_ok(b, bw, seg_h == 0 ? 8 : sh))
+  if (!batch_shape_ok(b, block_w == 0 ? 256 : bw, seg_h == 0 ? 8 : sh))
     return bfail(b, MLF_EINVAL, "launch shape gives too many work items");
   b->block_w = bw;
   b->seg_h = sh;
