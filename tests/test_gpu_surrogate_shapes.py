@@ -34,3 +34,26 @@ def test_prediction_is_the_same_in_every_batch(C, N, batches):
             ref = np.mean([v[1].astype(np.float64) for v in one[:b]], axis=0)
             assert abs(loss - np.mean([v[0] for v in one[:b]])) <= 1e-5 * loss
             assert np.linalg.norm(g - ref) <= 1e-4 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("C", [64, 128])
+def test_weight_gradient_slices(C):
+    """Slices of one chunk of pixels (one film) against slices of one or two,
+    two or three, three or four, and five or six: odd and even counts and the
+    repeated last chunk of the loads issued two ahead.  At most 2^13 FP32
+    additions in another order, tolerance as above."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2409_16659_amd import mlfilm
+
+    rng = np.random.default_rng(C)
+    s = mlfilm.Surrogate(1, 256, 256, width=C, blocks=2, batch=7, scale=1e-2)
+    s.set_params(rng.normal(0, 0.03, s.param_count).astype(np.float32))
+    h = torch.from_numpy((1.0 + 1e-2 * rng.normal(size=(7, 1, 256, 256))).astype(np.float32)).cuda()
+    h1 = h + 1e-3 * torch.randn(h.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    one = [s.gradient(h[i:i + 1], h1[i:i + 1])[1].astype(np.float64) for i in range(7)]
+    for b in (2, 3, 4, 7):
+        print(f"case C={C} batch {b}", flush=True)
+        g, ref = s.gradient(h[:b], h1[:b])[1], np.mean(one[:b], axis=0)
+        assert np.linalg.norm(g - ref) <= 1e-4 * np.linalg.norm(ref)
