@@ -689,8 +689,8 @@ constexpr int kSimds = 1024;  // MI355X: 256 CUs of four SIMDs
 bool fusable(const mlf_params& p) { return p.lattice == MLF_D2Q9 && p.tau == 1.0 && p.precision != MLF_F64; }
 
 // Steps that the strips of a film are cut for (two-step strips also serve
-// single steps).
-int strip_steps(const mlf_params& p) { return fusable(p) ? 2 : 1; }
+// single steps; stochastic rounding takes single steps only).
+int strip_steps(const mlf_params& p, bool sr = false) { return fusable(p) && !sr ? 2 : 1; }
 
 // Smallest segment height from which two steps go into one launch.  A launch
 // of two steps moves the populations once instead of twice, but a segment
@@ -703,27 +703,31 @@ int strip_steps(const mlf_params& p) { return fusable(p) ? 2 : 1; }
 int min_fused_rows(const mlf_params& p) { return p.precision == MLF_F32 ? 6 : 16; }
 
 // Segment height, for `tiles(height)` tiles over films of at most ny rows: the
-// lowest with at most one wavefront per SIMD, or, for films of two steps per
-// launch where that is above 12 rows, two (tall segments recompute little and
-// two wavefronts fill each other's waits; short ones recompute most of their
-// rows).  Even: the row loop takes two.  A tile more than fits costs a whole
+// lowest with at most one wavefront per SIMD, or, where that is above `most1`
+// rows, two (tall segments recompute little and two wavefronts fill each
+// other's waits; short ones recompute most of their rows).  Even: the row loop takes two.  A tile more than fits costs a whole
 // second round: 4096^2, 3 layers, 542 us per step at 152 rows (2052 tiles),
 // 413 at 158 (1976).  FP64 wavefronts keep a SIMD busy alone: 1000^2, 3
-// layers, 119 us at 18 rows (969 tiles), 125 at 10 (1700).
+// layers, 119 us at 18 rows (969 tiles), 125 at 10 (1700).  At one step per
+// launch (tau other than 1) a row costs half as much and the line lies higher:
+// FP32, 3 layers, 1024^2 59 us at 20 rows, 65 at 10; 2500 x 2900 426 at 122,
+// 386 at 62; f16mix, 2 layers, 902 x 2310 62.8 at 38, 50.3 at 20.
+int one_wave_rows(const mlf_params& p) { return p.precision == MLF_F64 ? 1 << 30 : fusable(p) ? 12 : 24; }
+
 template <typename F>
-int seg_for(F&& tiles, int ny, bool two) {
+int seg_for(F&& tiles, int ny, int most1) {
   auto lowest = [&](long long most) {
     int sh = 2;
     while (sh < ny && tiles(sh) > most) sh += 2;
     return sh;
   };
   int sh = lowest(kSimds);
-  if (two && sh > 12) sh = lowest(2 * kSimds);
+  if (sh > most1) sh = lowest(2 * kSimds);
   return std::max(1, std::min(sh, ny));
 }
 
-long long film_tiles(const mlf_params& p, int sh) {
-  return (long long)mlf::strip_count(p.nx, strip_steps(p)) * ((p.ny + sh - 1) / sh);
+long long film_tiles(const mlf_params& p, int sh, bool sr = false) {
+  return (long long)mlf::strip_count(p.nx, strip_steps(p, sr)) * ((p.ny + sh - 1) / sh);
 }
 
 // Wavefronts per workgroup.  Neighbouring strips in one workgroup march
@@ -734,7 +738,7 @@ long long film_tiles(const mlf_params& p, int sh) {
 // with one, 168 with four), as do films with fewer tiles than SIMDs but more
 // than CUs (777 x 515, 3 layers, FP64: 43.5 / 47.2 us).
 void default_launch(const mlf_params* p, int* bw, int* sh) {
-  *sh = seg_for([&](int s) { return film_tiles(*p, s); }, p->ny, fusable(*p));
+  *sh = seg_for([&](int s) { return film_tiles(*p, s); }, p->ny, one_wave_rows(*p));
   const int nstrip = mlf::strip_count(p->nx, strip_steps(*p));
   const long long t = film_tiles(*p, *sh);
   if (nstrip < 4 || (t > kSimds / 4 && t <= kSimds)) *bw = 64;
@@ -751,8 +755,8 @@ mlf::StepConsts<C> make_consts(const mlf_handle* h) {
   k.ny = p.ny;
   k.pitch = h->pitch;
   k.plane = (long long)h->plane;
-  k.wout = mlf::strip_width(p.nx, strip_steps(p));
-  k.nstrip = mlf::strip_count(p.nx, strip_steps(p));
+  k.wout = mlf::strip_width(p.nx, strip_steps(p, h->sr));
+  k.nstrip = mlf::strip_count(p.nx, strip_steps(p, h->sr));
   k.seg_h = h->seg_h;
   k.nseg = (p.ny + k.seg_h - 1) / k.seg_h;
   const int n = p.n_layers;
@@ -1380,7 +1384,7 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
   typedef std::array<int, 2> Cand;
   std::vector<Cand> cand;
   const int fixed[] = {2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 128};
-  const int nstrip = mlf::strip_count(p.nx, strip_steps(p));
+  const int nstrip = mlf::strip_count(p.nx, strip_steps(p, h->sr));
   for (int w : {64, 128, 192, 256, 512}) {
     if (w > max_block_w(p)) continue;
     for (int sh : fixed)
@@ -1998,7 +2002,7 @@ long long film_tiles(const mlf_batch* b, int f, int bw, int sh) {
   const mlf_params& p = b->film[f]->p;
   const int s = std::min(sh, p.ny);
   const int nw = bw / 64;
-  return (film_tiles(p, s) + nw - 1) / nw;
+  return (film_tiles(p, s, b->film[f]->sr) + nw - 1) / nw;
 }
 
 long long batch_items(const mlf_batch* b, int bw, int sh) {
@@ -2022,7 +2026,7 @@ int batch_default_seg(const mlf_batch* b) {
     for (const mlf_handle* h : b->film) t += film_tiles(h->p, s);
     return t;
   };
-  const int sh = seg_for(tiles, ny, fusable(b->p0));
+  const int sh = seg_for(tiles, ny, one_wave_rows(b->p0));
   return b->p0.precision == MLF_F64 ? std::min(sh, 32) : sh;
 }
 
@@ -2062,7 +2066,7 @@ mlf_status upload_table_t(mlf_batch* b) {
   // longest items first (layers x rows marched; the last segment of a film may
   // be short), so that the end of a launch is made of short ones
   std::vector<std::pair<int, int2>> cost;
-  const int nw = b->block_w / 64, halo = 2 * mlf::march_halo(strip_steps(b->p0));
+  const int nw = b->block_w / 64, halo = 2 * mlf::march_halo(strip_steps(b->p0, b->film[0]->sr));
   for (int f : b->order) {
     const mlf::StepConsts<C>& k = tab[f].kc;
     const int nt = (int)film_tiles(b, f, b->block_w, b->seg_h);

@@ -83,3 +83,20 @@ def test_guard_in_every_tile(mlf, where):
     ok.init(h0)
     ok.set_launch(64, 20)
     ok.step(64)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16mix", "f64"])
+@pytest.mark.parametrize("tau", [1.0, 1.3])
+@pytest.mark.parametrize("nx,ny", [(600, 2440), (600, 2450), (4, 3000)])
+def test_default_shapes_of_tall_films(mlf, prec, tau, nx, ny):
+    """The default launch on both sides of the line between one and two
+    wavefronts per SIMD: the same bits as in a fixed shape."""
+    film, h0 = _film(2, nx, ny, nx + ny)
+    film["tau"] = tau
+    print(f"case default shape {prec} tau={tau} {nx}x{ny}", flush=True)
+    a, b = mlf.Film(film, prec), mlf.Film(film, prec)
+    b.set_launch(128, 12)
+    for f in (a, b):
+        f.init(h0)
+        f.step(5)
+    assert np.array_equal(a.populations(), b.populations())
