@@ -736,14 +736,16 @@ long long film_tiles(const mlf_params& p, int sh, bool sr = false) {
 // with four, 570 with one.  16-bit storage is bound by arithmetic instead and
 // gains from tiles dealt out one by one (f16, 3 layers, 2900 x 2000: 151 us
 // with one, 168 with four), as do films with fewer tiles than SIMDs but more
-// than CUs (777 x 515, 3 layers, FP64: 43.5 / 47.2 us).
+// than CUs (777 x 515, 3 layers, FP64: 43.5 / 47.2 us).  At one step per launch
+// 16-bit films have half the arithmetic for their bytes and share again
+// (f16mix, 2 layers, 2912 x 1922, 48 rows: 144 us with one, 129 with four).
 void default_launch(const mlf_params* p, int* bw, int* sh) {
   *sh = seg_for([&](int s) { return film_tiles(*p, s); }, p->ny, one_wave_rows(*p));
   const int nstrip = mlf::strip_count(p->nx, strip_steps(*p));
   const long long t = film_tiles(*p, *sh);
   if (nstrip < 4 || (t > kSimds / 4 && t <= kSimds)) *bw = 64;
   else if (t <= kSimds || p->precision == MLF_F64) *bw = 256;
-  else *bw = p->precision == MLF_F32 ? 512 : 64;
+  else *bw = p->precision == MLF_F32 ? 512 : fusable(*p) ? 64 : 256;
 }
 
 template <typename C>
