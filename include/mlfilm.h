@@ -261,8 +261,8 @@ mlf_status mlf_get_rounding(const mlf_handle* h, int32_t* mode);
 mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* seg_h);
 
 /* Capture the launches of `steps` (even, > 0) consecutive steps into a HIP graph
- * that mlf_step replays whenever at least `steps` steps remain (guard polls
- * then fall on replay boundaries); 0 drops it.  The graph holds the step
+ * (one for either population buffer) that mlf_step replays whenever at least
+ * `steps` steps remain (guard polls then fall on replay boundaries); 0 drops it.  The graph holds the step
  * constants: mlf_init, mlf_init_device, mlf_load, mlf_set_launch and
  * mlf_autotune drop it.  EUNSUPPORTED on the default stream and for D1Q3
  * films (which already run many steps per launch). */

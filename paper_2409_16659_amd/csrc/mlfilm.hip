@@ -15,6 +15,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "advance.hpp"
 #include "d1q3_kernel.hpp"
 #include "d2q9_row_kernel.hpp"
 #include "stream_probe.hpp"
@@ -564,8 +565,8 @@ struct mlf_handle {
   int ahead;  // rows in flight asked for (mlf_set_prefetch; no effect on the kernel)
   int sr;     // stochastic rounding of the rest plane (16-bit storage)
   bool initialised;
-  hipGraphExec_t graph;  // captured step loop (constants baked in), or null
-  int graph_steps, graph_parity;
+  hipGraphExec_t graph[2];  // captured step loop by the buffer it starts from (constants baked in), or null
+  int graph_steps;
   std::string err;
 };
 
@@ -660,8 +661,10 @@ mlf_status fail(mlf_handle* h, mlf_status st, const std::string& m) {
 // The captured graph holds the step constants as kernel arguments: every
 // change of reference heights, scales or launch shape drops it.
 void drop_single_graph(mlf_handle* h) {
-  if (h->graph) (void)hipGraphExecDestroy(h->graph);
-  h->graph = nullptr;
+  for (hipGraphExec_t& g : h->graph) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
+  }
   h->graph_steps = 0;
 }
 
@@ -867,6 +870,28 @@ void by_storage(const mlf_handle* h, F&& f) {
 // one) and the segments are tall enough for it.
 int launch_steps(const mlf_handle* h, int64_t left) {
   return left >= 2 && fusable(h->p) && !h->sr && h->seg_h >= min_fused_rows(h->p) ? 2 : 1;
+}
+
+// Captures the launches of `steps` steps from buffer `cur`; next(left) gives
+// the steps of the next launch, launch(from, n) enqueues it.  Their number is
+// even, so that a replay leaves the populations in the buffer it started
+// from: the last two steps take a launch each where the pairs are odd.
+template <typename Next, typename Launch>
+hipError_t capture_steps(hipStream_t stream, int steps, int cur, Next&& next, Launch&& launch, hipGraphExec_t* out) {
+  hipError_t e = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal);
+  if (e != hipSuccess) return e;
+  for (int left = steps; left > 0 && e == hipSuccess; cur ^= 1) {
+    const int adv = steps % 4 == 2 && left <= 2 ? 1 : next(left);
+    e = launch(cur, adv);
+    left -= adv;
+  }
+  hipGraph_t g = nullptr;
+  const hipError_t end = hipStreamEndCapture(stream, &g);
+  if (e == hipSuccess) e = end;
+  if (e == hipSuccess) e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+  if (e != hipSuccess) *out = nullptr;
+  if (g) (void)hipGraphDestroy(g);
+  return e;
 }
 
 hipError_t launch_step(const mlf_handle* h, const void* src, void* dst, int steps) {
@@ -1278,9 +1303,8 @@ mlf_status mlf_create(const mlf_params* p, void* pop_a, void* pop_b, void* scrat
   for (int i = 0; i < kMaxLayers; ++i) h->hbar[i] = 0.0, h->scale[i] = 1.0;
   h->steps = 0;
   h->initialised = false;
-  h->graph = nullptr;
+  h->graph[0] = h->graph[1] = nullptr;
   h->graph_steps = 0;
-  h->graph_parity = 0;
   default_launch(p, &h->block_w, &h->seg_h);
   h->ahead = 1;
   h->sr = 0;
@@ -1540,7 +1564,7 @@ mlf_status mlf_step(mlf_handle* h, int64_t nsteps) {
   const int every = h->p.check_every;
   // D1Q3 films, and D2Q9 films one row high without a captured graph, run
   // many steps per launch with the film held in LDS
-  const bool row = !h->graph && row_resident(h->p);
+  const bool row = !h->graph_steps && row_resident(h->p);
   if (h->p.lattice == MLF_D1Q3 || row) {
     int64_t left = nsteps, since = 0;
     while (left > 0) {
@@ -1560,27 +1584,21 @@ mlf_status mlf_step(mlf_handle* h, int64_t nsteps) {
     }
     return every >= 0 ? check_guard(h) : MLF_OK;
   }
-  int64_t left = nsteps, since = 0;
-  while (left > 0) {
-    int64_t adv = 1;
-    if (h->graph && h->cur == h->graph_parity && left >= h->graph_steps) {
-      HIPCHK(hipGraphLaunch(h->graph, h->stream));
-      adv = h->graph_steps;
-    } else {
-      // two steps in one launch, but no further than the next guard poll
-      adv = launch_steps(h, every > 0 ? std::min<int64_t>(left, every - since) : left);
-      HIPCHK(launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1], (int)adv));
-      h->cur ^= 1;
-    }
-    left -= adv;
-    since += adv;
-    h->steps += adv;
-    if (every > 0 && since >= every && left > 0) {
-      since = 0;
-      mlf_status s = check_guard(h);
-      if (s != MLF_OK) return s;
-    }
-  }
+  const mlf_status st = mlf::advance(
+      nsteps, every, h->graph_steps, [&](int64_t room) { return launch_steps(h, room); },
+      [&]() {
+        HIPCHK(hipGraphLaunch(h->graph[h->cur], h->stream));
+        h->steps += h->graph_steps;
+        return MLF_OK;
+      },
+      [&](int adv) {
+        HIPCHK(launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1], adv));
+        h->cur ^= 1;
+        h->steps += adv;
+        return MLF_OK;
+      },
+      [&]() { return check_guard(h); });
+  if (st != MLF_OK) return st;
   if (every >= 0) return check_guard(h);
   return MLF_OK;
 }
@@ -1596,29 +1614,16 @@ mlf_status mlf_capture(mlf_handle* h, int32_t steps) {
   if (h->sr)
     return fail(h, MLF_EUNSUPPORTED, "stochastic rounding draws on the step count, which a graph would freeze");
   if (!h->stream) return fail(h, MLF_EUNSUPPORTED, "graph capture needs a non-default stream");
-  HIPCHK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-  hipError_t le = hipSuccess;
-  // an even number of launches, so that a replay leaves `cur` as it is: the
-  // last two steps take a launch each where their number is odd in pairs
-  int c = h->cur;
-  for (int left = steps; left > 0 && le == hipSuccess; c ^= 1) {
-    const int adv = steps % 4 == 2 && left <= 2 ? 1 : launch_steps(h, left);
-    le = launch_step(h, h->pop[c], h->pop[c ^ 1], adv);
-    left -= adv;
+  for (int c = 0; c < 2; ++c) {
+    const hipError_t e = capture_steps(
+        h->stream, steps, c, [&](int left) { return launch_steps(h, left); },
+        [&](int from, int adv) { return launch_step(h, h->pop[from], h->pop[from ^ 1], adv); }, &h->graph[c]);
+    if (e != hipSuccess) {
+      drop_single_graph(h);
+      return hip_check(h, e, "graph capture");
+    }
   }
-  hipGraph_t g = nullptr;
-  hipError_t ee = hipStreamEndCapture(h->stream, &g);
-  if (le != hipSuccess || ee != hipSuccess) {
-    if (g) (void)hipGraphDestroy(g);
-    return hip_check(h, le != hipSuccess ? le : ee, "graph capture");
-  }
-  hipGraphExec_t ex = nullptr;
-  hipError_t ie = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(g);
-  if (ie != hipSuccess) return hip_check(h, ie, "hipGraphInstantiate");
-  h->graph = ex;
   h->graph_steps = steps;
-  h->graph_parity = h->cur;
   return MLF_OK;
 }
 
@@ -1937,8 +1942,8 @@ struct mlf_batch {
   int max_nl;
   int n_items;
   bool table_dirty;
-  hipGraphExec_t graph;
-  int graph_steps, graph_parity;
+  hipGraphExec_t graph[2];  // as mlf_handle's
+  int graph_steps;
   int64_t steps;
   int failed;
   std::string err;
@@ -2179,8 +2184,10 @@ hipError_t launch_batch(const mlf_batch* b, int flip, int steps) {
 }
 
 void drop_graph(mlf_batch* b) {
-  if (b->graph) (void)hipGraphExecDestroy(b->graph);
-  b->graph = nullptr;
+  for (hipGraphExec_t& g : b->graph) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
+  }
   b->graph_steps = 0;
 }
 
@@ -2276,9 +2283,8 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
     return MLF_EUNSUPPORTED;
   }
   b->table_dirty = true;
-  b->graph = nullptr;
+  b->graph[0] = b->graph[1] = nullptr;
   b->graph_steps = 0;
-  b->graph_parity = 0;
   b->steps = 0;
   b->failed = -1;
   *out = b;
@@ -2407,20 +2413,21 @@ mlf_status mlf_batch_step(mlf_batch* b, int64_t nsteps) {
     }
     return batch_guard(b);
   }
-  int64_t left = nsteps;
-  while (left > 0) {
-    if (b->graph && b->cur == b->graph_parity && left >= b->graph_steps) {
-      BHIPCHK(hipGraphLaunch(b->graph, b->stream));
-      left -= b->graph_steps;
-      b->steps += b->graph_steps;
-    } else {
-      const int adv = batch_launch_steps(b, left);
-      BHIPCHK(launch_batch(b, b->cur, adv));
-      b->cur ^= 1;
-      left -= adv;
-      b->steps += adv;
-    }
-  }
+  st = mlf::advance(
+      nsteps, 0, b->graph_steps, [&](int64_t room) { return batch_launch_steps(b, room); },
+      [&]() {
+        BHIPCHK(hipGraphLaunch(b->graph[b->cur], b->stream));
+        b->steps += b->graph_steps;
+        return MLF_OK;
+      },
+      [&](int adv) {
+        BHIPCHK(launch_batch(b, b->cur, adv));
+        b->cur ^= 1;
+        b->steps += adv;
+        return MLF_OK;
+      },
+      [] { return MLF_OK; });
+  if (st != MLF_OK) return st;
   return batch_guard(b);
 }
 
@@ -2436,28 +2443,16 @@ mlf_status mlf_batch_capture(mlf_batch* b, int32_t steps) {
     return bfail(b, MLF_EUNSUPPORTED, "stochastic rounding draws from the step count, which a graph would freeze");
   mlf_status st = batch_ready(b);
   if (st != MLF_OK) return st;
-  BHIPCHK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-  hipError_t le = hipSuccess;
-  // an even number of launches, as in mlf_capture
-  int c = b->cur;
-  for (int left = steps; left > 0 && le == hipSuccess; c ^= 1) {
-    const int adv = steps % 4 == 2 && left <= 2 ? 1 : batch_launch_steps(b, left);
-    le = launch_batch(b, c, adv);
-    left -= adv;
+  for (int c = 0; c < 2; ++c) {
+    const hipError_t e = capture_steps(
+        b->stream, steps, c, [&](int left) { return batch_launch_steps(b, left); },
+        [&](int from, int adv) { return launch_batch(b, from, adv); }, &b->graph[c]);
+    if (e != hipSuccess) {
+      drop_graph(b);
+      return bhip(b, e, "graph capture");
+    }
   }
-  hipGraph_t g = nullptr;
-  hipError_t ee = hipStreamEndCapture(b->stream, &g);
-  if (le != hipSuccess || ee != hipSuccess) {
-    if (g) (void)hipGraphDestroy(g);
-    return bhip(b, le != hipSuccess ? le : ee, "graph capture");
-  }
-  hipGraphExec_t ex = nullptr;
-  hipError_t ie = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(g);
-  if (ie != hipSuccess) return bhip(b, ie, "hipGraphInstantiate");
-  b->graph = ex;
   b->graph_steps = steps;
-  b->graph_parity = b->cur;
   return MLF_OK;
 }
 
