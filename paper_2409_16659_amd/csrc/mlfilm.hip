@@ -815,10 +815,13 @@ hipError_t launch_st(const mlf_handle* h, const void* src, void* dst) {
                          kc);
       return hipGetLastError();
     }
-  hipLaunchKernelGGL((mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS>), dim3((unsigned)nblocks),
-                     dim3((unsigned)h->block_w), nw * mlf::march_lds<C>(NL, STEPS), h->stream,
-                     static_cast<const unsigned char*>(src),
-                     static_cast<unsigned char*>(dst), kc);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3((unsigned)h->block_w), nw * mlf::march_lds<C>(NL, STEPS),
+                       h->stream, static_cast<const unsigned char*>(src), static_cast<unsigned char*>(dst), kc);
+  };
+  constexpr int kNarrow = mlf::step_lanes<C, NL>(256), kWide = mlf::step_lanes<C, NL>(512);
+  if (h->block_w <= 256) launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kNarrow>);
+  else launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kWide>);
   return hipGetLastError();
 }
 
@@ -1324,7 +1327,7 @@ int64_t mlf_steps_done(const mlf_handle* h) { return h ? h->steps : -1; }
 const char* mlf_last_error(const mlf_handle* h) { return h ? h->err.c_str() : "null handle"; }
 
 // Widest strip the step kernel is compiled for with these parameters (the
-// kernel's step_max_lanes: FP64 with four layers stops at 256 lanes).
+// kernel's step_lanes: FP64 with four layers stops at 256 lanes).
 int max_block_w(const mlf_params& p) { return (p.precision == MLF_F64 && p.n_layers == 4) ? 256 : 512; }
 
 mlf_status mlf_set_launch(mlf_handle* h, int32_t block_w, int32_t seg_h) {

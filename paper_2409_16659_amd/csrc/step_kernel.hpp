@@ -1301,22 +1301,23 @@ __device__ inline void march_tile(const unsigned char* __restrict__ src, unsigne
   else if (low) kc.flag[0] = 1;
 }
 
-// Lanes of the largest workgroup the step kernels are compiled for: 512 (two
-// waves per SIMD, at most 256 VGPRs each), except FP64 arithmetic on four
-// layers, whose working set needs more registers than that and keeps one
-// wave per SIMD (256 lanes).
+// Lanes of the workgroups that the step kernel is compiled for: 512 (at most
+// 256 registers per lane) or, where that is not enough for the working set
+// with a row ahead, 256 (512 registers, one wavefront per SIMD).  FP64
+// arithmetic on four layers needs the latter everywhere; on three layers
+// (274 registers) it serves workgroups of up to 256 lanes, and wider ones
+// load each row when they come to it, since the row ahead would spill: 2048 x
+// 2048 at 256 x 40 394 us per step against 414 without the row ahead, 1000 x
+// 1000 at 256 x 18 103.5 / 112.6, 777 x 515 at 64 x 10 36.0 / 38.1.
 template <typename C, int NL>
-constexpr int step_max_lanes() {
-  return (sizeof(C) == 8 && NL == 4) ? 256 : 512;
+constexpr int step_lanes(int block_w) {
+  return sizeof(C) == 8 && (NL == 4 || (NL == 3 && block_w <= 256)) ? 256 : 512;
 }
 
-template <typename R, typename S, typename C, int NL, bool TAU1, int EA, int EB, int STEPS>
-__global__ void __launch_bounds__((step_max_lanes<C, NL>()))
+template <typename R, typename S, typename C, int NL, bool TAU1, int EA, int EB, int STEPS, int LANES>
+__global__ void __launch_bounds__(LANES)
 step_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst, const StepConsts<C> kc) {
-  // FP64 with three layers: the 54 registers of a row ahead would spill, and
-  // the second wavefront of a SIMD hides its loads (777 x 515 38.7 us per
-  // step, 43.5 with a row ahead)
-  constexpr bool kAhead = !(sizeof(C) == 8 && NL == 3);
+  constexpr bool kAhead = !(sizeof(C) == 8 && NL == 3 && LANES == 512);
   const int group = tile_of_block(blockIdx.x, gridDim.x);
   const int nw = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (group * nw >= kc.nstrip * kc.nseg) return;  // padding workgroup (uniform)
@@ -1327,7 +1328,7 @@ step_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ d
 
 // The same for a film one row high (FP64 or FP32 storage).
 template <typename C, int NL, bool TAU1, int EA, int EB, int STEPS>
-__global__ void __launch_bounds__((step_max_lanes<C, NL>()))
+__global__ void __launch_bounds__(512)
 row_step_kernel(const C* __restrict__ src, C* __restrict__ dst, const StepConsts<C> kc) {
   const int tile = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   row_tile<C, NL, TAU1, EA, EB, STEPS>(src, dst, kc, tile);
