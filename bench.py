@@ -184,11 +184,10 @@ def steps_per_launch(film, prec, launch):
 
 def step_grid_threads(film, prec, launch):
     """Work-items of one step_kernel dispatch of this film and launch shape:
-    a wavefront per tile (54 columns where the film can take two steps per
-    launch, else 60, by seg_h rows), the grid padded to a multiple of the 8
-    XCDs."""
+    a wavefront per tile (54 columns where it takes two steps, else 60, by
+    seg_h rows), the grid padded to a multiple of the 8 XCDs."""
     w, sh = launch[0], launch[1]
-    cols = 54 if film["tau"] == 1.0 and prec != "f64" else 60
+    cols = 54 if steps_per_launch(film, prec, launch) == 2 else 60
     n = -(-film["nx"] // cols)
     strips = -(-film["nx"] // -(-film["nx"] // n))
     groups = -(-strips * -(-film["ny"] // sh) // (w // 64))

@@ -211,12 +211,16 @@ mlf_status mlf_load(mlf_handle* h, const void* blob, size_t bytes);
  *
  * Launch shape of the step kernel: block_w threads (64, 128, 192, 256 or 512;
  * 512 is MLF_EINVAL for FP64 films of four layers, whose kernel is compiled
- * for at most 256), each wavefront of 64 taking one tile, a strip of 60
- * columns (54 for films that can run two steps per launch: tau = 1, storage
- * other than MLF_F64) by seg_h rows (>= 1).  Tall enough segments run two
- * steps per launch.  Results do not depend on the shape.  0 = default,
- * chosen by the film's size.  D1Q3 films keep their fixed kernel shapes
- * (the values are stored and ignored; mlf_autotune returns them unchanged). */
+ * for at most 256), each wavefront of 64 taking one tile, a strip of columns
+ * by seg_h rows (>= 1).  Films with tau = 1 and storage other than MLF_F64 run
+ * two steps per launch where segments are at least 6 rows (MLF_F32) or 16 rows
+ * high (16-bit storage), on strips of up to 54 columns; all other launches take
+ * one step on strips of up to 60.  Results do not depend on the shape.  0 =
+ * default, chosen by the film's size, for launches of two steps and of one
+ * separately; a value set here holds for both, and mlf_get_launch returns the
+ * shape of two steps where the film takes them.  D1Q3 films keep their fixed
+ * kernel shapes (the values are stored and ignored; mlf_autotune returns them
+ * unchanged). */
 mlf_status mlf_set_launch(mlf_handle* h, int32_t block_w, int32_t seg_h);
 mlf_status mlf_get_launch(const mlf_handle* h, int32_t* block_w, int32_t* seg_h);
 
@@ -256,8 +260,9 @@ mlf_status mlf_get_rounding(const mlf_handle* h, int32_t* mode);
  * the four fastest are then re-timed twice with 4 x reps launches each and
  * the smallest time per step wins.  Candidates: block_w in {64, 128, 192,
  * 256, 512} (not 512 for FP64 films of four layers), segment heights from a
- * fixed list plus those that give one to four wavefronts per SIMD.
- * Synchronises. */
+ * fixed list plus those that give one to four wavefronts per SIMD.  A shape
+ * that wins with two steps per launch leaves the shape of single steps (the
+ * last of an odd number) as it was.  Synchronises. */
 mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* seg_h);
 
 /* Capture the launches of `steps` (even, > 0) consecutive steps into a HIP graph

@@ -549,6 +549,11 @@ __global__ void finish_min(const double* __restrict__ part, double* __restrict__
 
 }  // namespace
 
+// Launch shape of the step kernel: lanes per workgroup, rows per segment.
+struct Shape {
+  int w, h;
+};
+
 struct mlf_handle {
   mlf_params p;
   void* pop[2];
@@ -561,7 +566,7 @@ struct mlf_handle {
   double hbar[kMaxLayers];
   double scale[kMaxLayers];  // storage scale per layer (1 except IEEE half)
   int64_t steps;
-  int block_w, seg_h;
+  Shape two, one;  // shapes of launches of two steps (also decides on them) and of one
   int ahead;  // rows in flight asked for (mlf_set_prefetch; no effect on the kernel)
   int sr;     // stochastic rounding of the rest plane (16-bit storage)
   bool initialised;
@@ -691,10 +696,6 @@ constexpr int kSimds = 1024;  // MI355X: 256 CUs of four SIMDs
 // would need more registers than two waves per SIMD have).
 bool fusable(const mlf_params& p) { return p.lattice == MLF_D2Q9 && p.tau == 1.0 && p.precision != MLF_F64; }
 
-// Steps that the strips of a film are cut for (two-step strips also serve
-// single steps; stochastic rounding takes single steps only).
-int strip_steps(const mlf_params& p, bool sr = false) { return fusable(p) && !sr ? 2 : 1; }
-
 // Smallest segment height from which two steps go into one launch.  A launch
 // of two steps moves the populations once instead of twice, but a segment
 // recomputes ten rows instead of four, so short segments (small films, which
@@ -705,54 +706,98 @@ int strip_steps(const mlf_params& p, bool sr = false) { return fusable(p) && !sr
 // f16mix, 4 layers, 768^2 (12 rows) 33.5 / 35.7, 1500^2 (21 rows) 94 / 80.
 int min_fused_rows(const mlf_params& p) { return p.precision == MLF_F32 ? 6 : 16; }
 
-// Segment height, for `tiles(height)` tiles over films of at most ny rows: the
-// lowest with at most one wavefront per SIMD, or, where that is above `most1`
-// rows, two (tall segments recompute little and two wavefronts fill each
-// other's waits; short ones recompute most of their rows).  Even: the row loop takes two.  A tile more than fits costs a whole
-// second round: 4096^2, 3 layers, 542 us per step at 152 rows (2052 tiles),
-// 413 at 158 (1976).  FP64 wavefronts keep a SIMD busy alone: 1000^2, 3
-// layers, 119 us at 18 rows (969 tiles), 125 at 10 (1700).  At one step per
-// launch (tau other than 1) a row costs half as much and the line lies higher:
-// FP32, 3 layers, 1024^2 59 us at 20 rows, 65 at 10; 2500 x 2900 426 at 122,
-// 386 at 62; f16mix, 2 layers, 902 x 2310 62.8 at 38, 50.3 at 20.
-int one_wave_rows(const mlf_params& p) { return p.precision == MLF_F64 ? 1 << 30 : fusable(p) ? 12 : 24; }
-
+// Lowest even segment height (at most ny) with at most `most` tiles, by
+// bisection: tiles(height) does not grow with the height.  Even: the row loop
+// takes two.
 template <typename F>
-int seg_for(F&& tiles, int ny, int most1) {
-  auto lowest = [&](long long most) {
-    int sh = 2;
-    while (sh < ny && tiles(sh) > most) sh += 2;
-    return sh;
-  };
-  int sh = lowest(kSimds);
-  if (sh > most1) sh = lowest(2 * kSimds);
-  return std::max(1, std::min(sh, ny));
+int lowest_seg(F&& tiles, int ny, long long most) {
+  int lo = 1, hi = std::max(1, (ny + 1) / 2);
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    if (tiles(2 * mid) <= most) hi = mid;
+    else lo = mid + 1;
+  }
+  return std::min(2 * lo, ny);
 }
 
-long long film_tiles(const mlf_params& p, int sh, bool sr = false) {
-  return (long long)mlf::strip_count(p.nx, strip_steps(p, sr)) * ((p.ny + sh - 1) / sh);
+// Segment height of launches of two steps: the lowest with at most one
+// wavefront per SIMD, or, where that is above 12 rows, two (tall segments
+// recompute little and two wavefronts fill each other's waits; short ones
+// recompute most of their rows).  A tile more than fits costs a whole second
+// round: 4096^2, 3 layers, 542 us per step at 152 rows (2052 tiles), 413 at
+// 158 (1976).
+template <typename F>
+int two_step_seg(F&& tiles, int ny) {
+  const int h = lowest_seg(tiles, ny, kSimds);
+  return h > 12 ? lowest_seg(tiles, ny, 2 * kSimds) : h;
 }
 
-// Wavefronts per workgroup.  Neighbouring strips in one workgroup march
+long long film_tiles(const mlf_params& p, int sh, int steps) {
+  return (long long)mlf::strip_count(p.nx, steps) * ((p.ny + sh - 1) / sh);
+}
+
+// Shape of launches of two steps.  Neighbouring strips in one workgroup march
 // together and share the columns that both read, which pays where the film
-// streams from HBM: FP32, 4096^2, 3 layers, 388 us per step with eight, 412
-// with four, 570 with one.  16-bit storage is bound by arithmetic instead and
-// gains from tiles dealt out one by one (f16, 3 layers, 2900 x 2000: 151 us
-// with one, 168 with four), as do films with fewer tiles than SIMDs but more
-// than CUs (777 x 515, 3 layers, FP64: 43.5 / 47.2 us).  At one step per launch
-// 16-bit films have half the arithmetic for their bytes and share again
-// (f16mix, 2 layers, 2912 x 1922, 48 rows: 144 us with one, 129 with four).
-void default_launch(const mlf_params* p, int* bw, int* sh) {
-  *sh = seg_for([&](int s) { return film_tiles(*p, s); }, p->ny, one_wave_rows(*p));
-  const int nstrip = mlf::strip_count(p->nx, strip_steps(*p));
-  const long long t = film_tiles(*p, *sh);
-  if (nstrip < 4 || (t > kSimds / 4 && t <= kSimds)) *bw = 64;
-  else if (t <= kSimds || p->precision == MLF_F64) *bw = 256;
-  else *bw = p->precision == MLF_F32 ? 512 : fusable(*p) ? 64 : 256;
+// streams from HBM: FP32, 4096^2, 3 layers, 388 us per step with eight
+// wavefronts per workgroup, 412 with four, 570 with one.  16-bit storage is
+// bound by arithmetic instead and gains from tiles dealt out one by one (f16,
+// 3 layers, 2900 x 2000: 151 us with one, 168 with four), as do films with
+// fewer tiles than SIMDs but more than CUs.
+Shape two_step_shape(const mlf_params& p) {
+  Shape s;
+  s.h = two_step_seg([&](int h) { return film_tiles(p, h, 2); }, p.ny);
+  const long long t = film_tiles(p, s.h, 2);
+  if (mlf::strip_count(p.nx, 2) < 4 || (t > kSimds / 4 && t <= kSimds)) s.w = 64;
+  else s.w = t <= kSimds ? 256 : p.precision == MLF_F32 ? 512 : 64;
+  return s;
+}
+
+constexpr size_t kInfinityCache = 256u << 20;
+
+// Shape of launches of one step.  Where the two buffers fit into the Infinity
+// Cache, tiles are dealt out one by one, at most one per SIMD (two with 16-bit
+// storage, whose rows load half as much): 777 x 515, 3 layers, FP64 (8 rows)
+// 37.1 us per step with one wavefront per workgroup, 38.0 with four; f16mix, 2
+// layers, 2989 x 444 26.1 us with two per SIMD (12 rows), 30.6 with one (24).
+// Films that stream from HBM take four strips side by side in a workgroup,
+// which share the columns that both read, and segments of at most 80 rows in
+// whole rounds of workgroups: FP64, 4 layers, 2596 x 1399 455 us at 32 rows (two
+// rounds), 503 at 40, 645 at 56 (1.1 rounds; 597 with two strips, 582 with
+// one).  A round is a little less than one wavefront per SIMD.  Eight strips
+// and taller segments pay in 16-bit films, two full wavefronts per SIMD to the
+// round (f16mix, 4 layers, 4096^2 579 us at 512 x 142, 615 at 256 x 70), and in
+// FP32 films from 1 GiB on (4096^2, one layer 277 us at 512 x 76, 290 at 256 x
+// 76; 3 layers 793 / 815; 4000 x 3000 555 at 512 x 116, 568 at 256 x 68, 661 at
+// 512 x 100: 2010 tiles).  FP64 films only just beyond the cache do best with
+// three strips and one workgroup per CU: 900 x 700, 4 layers, 84 us at 192 x
+// 14, 92 at 256 x 12.
+Shape one_step_shape(const mlf_params& p) {
+  const bool half = p.precision != MLF_F64 && p.precision != MLF_F32;
+  const size_t bytes = 2 * buffer_bytes(p.precision, p.n_layers, (size_t)pitch_of(&p) * p.ny, nq_of(&p));
+  auto tiles = [&](int h) { return film_tiles(p, h, 1); };
+  if (bytes <= kInfinityCache) return {64, lowest_seg(tiles, p.ny, half ? 2 * kSimds : kSimds)};
+  const bool wide = half || (p.precision == MLF_F32 && bytes >= 4 * kInfinityCache);
+  const int most = half ? 160 : wide ? 110 : 80;
+  const long long round = half ? 2 * kSimds : (wide ? 2 : 1) * kSimds * 15 / 16;
+  Shape s{wide ? 512 : 256, lowest_seg(tiles, p.ny, (tiles(most) + round - 1) / round * round)};
+  if (p.precision == MLF_F64 && s.h <= 20) s = {192, lowest_seg(tiles, p.ny, kSimds * 3 / 4)};
+  if (mlf::strip_count(p.nx, 1) < 4) s.w = 64;  // too few strips to share anything
+  return s;
+}
+
+// Default shapes of a film: of launches of two steps and of one.  A film whose
+// segments would be too short for two steps takes single ones only.
+void default_launch(const mlf_params& p, Shape* two, Shape* one) {
+  *one = one_step_shape(p);
+  *two = fusable(p) ? two_step_shape(p) : *one;
+  if (fusable(p) && two->h < min_fused_rows(p)) {
+    one->h = std::min(one->h, min_fused_rows(p) - 2);
+    *two = *one;
+  }
 }
 
 template <typename C>
-mlf::StepConsts<C> make_consts(const mlf_handle* h) {
+mlf::StepConsts<C> make_consts(const mlf_handle* h, Shape shape, int steps) {
   const mlf_params& p = h->p;
   mlf::StepConsts<C> k;
   std::memset(&k, 0, sizeof(k));
@@ -760,9 +805,9 @@ mlf::StepConsts<C> make_consts(const mlf_handle* h) {
   k.ny = p.ny;
   k.pitch = h->pitch;
   k.plane = (long long)h->plane;
-  k.wout = mlf::strip_width(p.nx, strip_steps(p, h->sr));
-  k.nstrip = mlf::strip_count(p.nx, strip_steps(p, h->sr));
-  k.seg_h = h->seg_h;
+  k.wout = mlf::strip_width(p.nx, steps);
+  k.nstrip = mlf::strip_count(p.nx, steps);
+  k.seg_h = shape.h;
   k.nseg = (p.ny + k.seg_h - 1) / k.seg_h;
   const int n = p.n_layers;
   double z[kMaxLayers + 1];
@@ -803,24 +848,24 @@ mlf::StepConsts<C> make_consts(const mlf_handle* h) {
 
 template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB, int STEPS>
 hipError_t launch_st(const mlf_handle* h, const void* src, void* dst) {
-  mlf::StepConsts<C> kc = make_consts<C>(h);
-  const size_t nw = h->block_w / 64;
+  const Shape shape = STEPS == 2 ? h->two : h->one;
+  mlf::StepConsts<C> kc = make_consts<C>(h, shape, STEPS);
+  const size_t nw = shape.w / 64;
   // grid padded to a multiple of the XCD count (tile_of_block)
   const int ngroups = (kc.nstrip * kc.nseg + (int)nw - 1) / (int)nw;
   const int nblocks = (ngroups + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
   if constexpr (std::is_same_v<R, C> && std::is_same_v<S, C>)
     if (h->p.ny == 1) {
       hipLaunchKernelGGL((mlf::row_step_kernel<C, NL, T1, EA, EB, STEPS>), dim3((unsigned)ngroups),
-                         dim3((unsigned)h->block_w), 0, h->stream, static_cast<const C*>(src), static_cast<C*>(dst),
-                         kc);
+                         dim3((unsigned)shape.w), 0, h->stream, static_cast<const C*>(src), static_cast<C*>(dst), kc);
       return hipGetLastError();
     }
   auto launch = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3((unsigned)h->block_w), nw * mlf::march_lds<C>(NL, STEPS),
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3((unsigned)shape.w), nw * mlf::march_lds<C>(NL, STEPS),
                        h->stream, static_cast<const unsigned char*>(src), static_cast<unsigned char*>(dst), kc);
   };
   constexpr int kNarrow = mlf::step_lanes<C, NL>(256), kWide = mlf::step_lanes<C, NL>(512);
-  if (h->block_w <= 256) launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kNarrow>);
+  if (shape.w <= 256) launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kNarrow>);
   else launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kWide>);
   return hipGetLastError();
 }
@@ -872,7 +917,7 @@ void by_storage(const mlf_handle* h, F&& f) {
 // film can (stochastic rounding draws on every step's count and stays at
 // one) and the segments are tall enough for it.
 int launch_steps(const mlf_handle* h, int64_t left) {
-  return left >= 2 && fusable(h->p) && !h->sr && h->seg_h >= min_fused_rows(h->p) ? 2 : 1;
+  return left >= 2 && fusable(h->p) && !h->sr && h->two.h >= min_fused_rows(h->p) ? 2 : 1;
 }
 
 // Captures the launches of `steps` steps from buffer `cur`; next(left) gives
@@ -926,7 +971,7 @@ bool d1_tiled(const mlf_params& p) { return p.lattice == MLF_D1Q3 && p.nx > mlf:
 
 template <typename C, int NL, bool T1, int EA, int EB>
 hipError_t d1_launch_nl(mlf_handle* h, int steps) {
-  mlf::StepConsts<C> kc = make_consts<C>(h);
+  mlf::StepConsts<C> kc = make_consts<C>(h, h->one, 1);
   const mlf_params& p = h->p;
   const C* src = static_cast<const C*>(h->pop[h->cur]);
   C* dst = static_cast<C*>(h->pop[h->cur ^ 1]);
@@ -994,7 +1039,7 @@ bool row_resident(const mlf_params& p) {
 
 template <typename C, int NL, bool T1, int EA, int EB>
 hipError_t row_launch_nl(mlf_handle* h, int steps) {
-  mlf::StepConsts<C> kc = make_consts<C>(h);
+  mlf::StepConsts<C> kc = make_consts<C>(h, h->one, 1);
   const mlf_params& p = h->p;
   if (row_tiled(p)) {
     if (steps < 1 || steps > mlf::kRowTileSteps) return hipErrorInvalidValue;
@@ -1308,7 +1353,7 @@ mlf_status mlf_create(const mlf_params* p, void* pop_a, void* pop_b, void* scrat
   h->initialised = false;
   h->graph[0] = h->graph[1] = nullptr;
   h->graph_steps = 0;
-  default_launch(p, &h->block_w, &h->seg_h);
+  default_launch(*p, &h->two, &h->one);
   h->ahead = 1;
   h->sr = 0;
   *out = h;
@@ -1333,28 +1378,28 @@ int max_block_w(const mlf_params& p) { return (p.precision == MLF_F64 && p.n_lay
 mlf_status mlf_set_launch(mlf_handle* h, int32_t block_w, int32_t seg_h) {
   if (!h) return MLF_EINVAL;
   drop_single_graph(h);
-  int bw, sh;
-  default_launch(&h->p, &bw, &sh);
+  Shape two, one;
+  default_launch(h->p, &two, &one);
   if (block_w != 0) {
     if (block_w != 64 && block_w != 128 && block_w != 192 && block_w != 256 && block_w != 512)
       return fail(h, MLF_EINVAL, "block_w must be 64, 128, 192, 256 or 512");
     if (block_w > max_block_w(h->p))
       return fail(h, MLF_EINVAL, "block_w 512 is not available for FP64 films of four layers");
-    bw = block_w;
+    two.w = one.w = block_w;
   }
   if (seg_h != 0) {
     if (seg_h < 1) return fail(h, MLF_EINVAL, "seg_h must be >= 1");
-    sh = std::min(seg_h, h->p.ny);
+    two.h = one.h = std::min(seg_h, h->p.ny);
   }
-  h->block_w = bw;
-  h->seg_h = sh;
+  h->two = two;
+  h->one = one;
   return MLF_OK;
 }
 
 mlf_status mlf_get_launch(const mlf_handle* h, int32_t* block_w, int32_t* seg_h) {
   if (!h) return MLF_EINVAL;
-  if (block_w) *block_w = h->block_w;
-  if (seg_h) *seg_h = h->seg_h;
+  if (block_w) *block_w = h->two.w;
+  if (seg_h) *seg_h = h->two.h;
   return MLF_OK;
 }
 
@@ -1402,18 +1447,18 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
   if (!h || reps < 1) return MLF_EINVAL;
   if (!h->initialised) return fail(h, MLF_EINVAL, "autotune before init");
   if (h->p.lattice == MLF_D1Q3) {  // the D1Q3 kernels have fixed shapes
-    if (block_w) *block_w = h->block_w;
-    if (seg_h) *seg_h = h->seg_h;
+    if (block_w) *block_w = h->two.w;
+    if (seg_h) *seg_h = h->two.h;
     return MLF_OK;
   }
   drop_single_graph(h);
   const mlf_params& p = h->p;
-  const int keep_w = h->block_w, keep_h = h->seg_h;
+  const Shape keep_two = h->two, keep_one = h->one;
   // candidates (block width, segment height)
   typedef std::array<int, 2> Cand;
   std::vector<Cand> cand;
   const int fixed[] = {2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 128};
-  const int nstrip = mlf::strip_count(p.nx, strip_steps(p, h->sr));
+  const int nstrip = mlf::strip_count(p.nx, fusable(p) && !h->sr ? 2 : 1);
   for (int w : {64, 128, 192, 256, 512}) {
     if (w > max_block_w(p)) continue;
     for (int sh : fixed)
@@ -1433,8 +1478,7 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
   // ms per step of candidate c over n launches (current -> other buffer,
   // never swapped: the state is left unchanged)
   auto time_of = [&](const Cand& c, int n, float* ms) {
-    h->block_w = c[0];
-    h->seg_h = c[1];
+    h->two = h->one = Shape{c[0], c[1]};
     const int adv = launch_steps(h, 2);
     if ((st = hip_check(h, launch_step(h, h->pop[h->cur], h->pop[h->cur ^ 1], adv), "autotune launch")) != MLF_OK)
       return false;
@@ -1457,7 +1501,7 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
     if (!time_of(c, reps, &ms)) break;
     timed.emplace_back(ms, c);
   }
-  int bw = keep_w, bh = keep_h;
+  Shape best_shape = keep_two;
   if (st == MLF_OK && !timed.empty()) {
     std::sort(timed.begin(), timed.end());
     timed.resize(std::min<size_t>(timed.size(), 4));
@@ -1468,16 +1512,16 @@ mlf_status mlf_autotune(mlf_handle* h, int32_t reps, int32_t* block_w, int32_t* 
         if (time_of(timed[i].second, 4 * reps, &ms)) best[i] = std::min(best[i], ms);
       }
     const size_t k = (size_t)(std::min_element(best.begin(), best.end()) - best.begin());
-    bw = timed[k].second[0];
-    bh = timed[k].second[1];
+    best_shape = Shape{timed[k].second[0], timed[k].second[1]};
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  h->block_w = (st == MLF_OK) ? bw : keep_w;
-  h->seg_h = (st == MLF_OK) ? bh : keep_h;
+  h->two = (st == MLF_OK) ? best_shape : keep_two;
+  // a shape tuned for two steps leaves that of a step left over as it was
+  h->one = (st == MLF_OK && launch_steps(h, 2) == 1) ? best_shape : keep_one;
   if (st != MLF_OK) return st;
-  if (block_w) *block_w = bw;
-  if (seg_h) *seg_h = bh;
+  if (block_w) *block_w = best_shape.w;
+  if (seg_h) *seg_h = best_shape.h;
   return MLF_OK;
 }
 
@@ -2007,12 +2051,18 @@ size_t batch_table_entry(const mlf_batch* b) {
 
 int* batch_flags(mlf_batch* b) { return reinterpret_cast<int*>(b->scratch + kBatchFlagOff); }
 
+// Steps of the batch's launches, and so of its strips, with segments of `sh`
+// rows (a step left over runs on the same strips).
+int batch_steps(const mlf_batch* b, int sh) {
+  return fusable(b->p0) && !b->film[0]->sr && sh >= min_fused_rows(b->p0) ? 2 : 1;
+}
+
 // Work items (workgroups) of film f under the batch's launch shape.
 long long film_tiles(const mlf_batch* b, int f, int bw, int sh) {
   const mlf_params& p = b->film[f]->p;
   const int s = std::min(sh, p.ny);
   const int nw = bw / 64;
-  return (film_tiles(p, s, b->film[f]->sr) + nw - 1) / nw;
+  return (film_tiles(p, s, batch_steps(b, sh)) + nw - 1) / nw;
 }
 
 long long batch_items(const mlf_batch* b, int bw, int sh) {
@@ -2031,12 +2081,16 @@ long long batch_items(const mlf_batch* b, int bw, int sh) {
 int batch_default_seg(const mlf_batch* b) {
   int ny = 1;
   for (const mlf_handle* h : b->film) ny = std::max(ny, h->p.ny);
-  auto tiles = [&](int s) {
-    long long t = 0;
-    for (const mlf_handle* h : b->film) t += film_tiles(h->p, s);
-    return t;
+  auto seg = [&](int steps) {
+    auto tiles = [&](int s) {
+      long long t = 0;
+      for (const mlf_handle* h : b->film) t += film_tiles(h->p, s, steps);
+      return t;
+    };
+    return steps == 2 ? two_step_seg(tiles, ny) : lowest_seg(tiles, ny, kSimds);
   };
-  const int sh = seg_for(tiles, ny, one_wave_rows(b->p0));
+  const int sh = seg(fusable(b->p0) ? 2 : 1);
+  if (fusable(b->p0) && sh < min_fused_rows(b->p0)) return std::min(seg(1), min_fused_rows(b->p0) - 2);
   return b->p0.precision == MLF_F64 ? std::min(sh, 32) : sh;
 }
 
@@ -2065,10 +2119,8 @@ mlf_status upload_table_t(mlf_batch* b) {
   items.reserve((size_t)b->n_items);
   for (int f = 0; f < b->n; ++f) {
     mlf_handle* h = b->film[f];
-    h->block_w = b->block_w;
-    h->seg_h = std::min(b->seg_h, h->p.ny);
     std::memset(&tab[f], 0, sizeof(tab[f]));
-    tab[f].kc = make_consts<C>(h);
+    tab[f].kc = make_consts<C>(h, Shape{b->block_w, std::min(b->seg_h, h->p.ny)}, batch_steps(b, b->seg_h));
     tab[f].kc.flag = batch_flags(b) + f;
     tab[f].offset = (long long)b->offset[f];
     tab[f].nl = h->p.n_layers;
@@ -2076,7 +2128,7 @@ mlf_status upload_table_t(mlf_batch* b) {
   // longest items first (layers x rows marched; the last segment of a film may
   // be short), so that the end of a launch is made of short ones
   std::vector<std::pair<int, int2>> cost;
-  const int nw = b->block_w / 64, halo = 2 * mlf::march_halo(strip_steps(b->p0, b->film[0]->sr));
+  const int nw = b->block_w / 64, halo = 2 * mlf::march_halo(batch_steps(b, b->seg_h));
   for (int f : b->order) {
     const mlf::StepConsts<C>& k = tab[f].kc;
     const int nt = (int)film_tiles(b, f, b->block_w, b->seg_h);
@@ -2171,7 +2223,7 @@ hipError_t d1_batch_launch(const mlf_batch* b, int steps) {
 
 // Steps of the next launch of the batch (as launch_steps for one film).
 int batch_launch_steps(const mlf_batch* b, int64_t left) {
-  return left >= 2 && fusable(b->p0) && !b->film[0]->sr && b->seg_h >= min_fused_rows(b->p0) ? 2 : 1;
+  return left >= 2 ? batch_steps(b, b->seg_h) : 1;
 }
 
 // `steps` steps of every film from buffer `flip` into the other one.

@@ -1,0 +1,81 @@
+"""Default launch shapes, read back without a GPU: segments are the lowest
+even heights that keep the tiles within the rule's count, restated here
+without its bisection, over films of every storage format on both sides of
+each line of the rule."""
+import ctypes as C
+import random
+
+import pytest
+
+from paper_2409_16659_amd import inputs, mlfilm
+
+SIMDS, CACHE = 1024, 256 << 20
+
+
+def default_launch(film, precision):
+    lib = mlfilm.load_library()
+    p = mlfilm.make_params(film, precision, allow_unstable=True)
+    h, w, s = C.c_void_p(), C.c_int32(), C.c_int32()
+    assert lib.mlf_create(C.byref(p), C.c_void_p(1 << 20), C.c_void_p(2 << 20), C.c_void_p(3 << 20), None,
+                          C.byref(h)) == 0
+    assert lib.mlf_get_launch(h, C.byref(w), C.byref(s)) == 0
+    lib.mlf_destroy(h)
+    return w.value, s.value, 2 * mlfilm.query_sizes(p)[0]
+
+
+def strips(nx, cols):
+    n = -(-nx // cols)
+    return -(-nx // -(-nx // n))
+
+
+def lowest(nx, ny, cols, most):
+    h = 2
+    while h < ny and strips(nx, cols) * -(-ny // h) > most:
+        h += 2
+    return min(h, ny)
+
+
+def one_step(nx, ny, precision, nbytes):
+    half = precision not in ("f64", "f32")
+    if nbytes <= CACHE:
+        return 64, lowest(nx, ny, 60, (2 if half else 1) * SIMDS)
+    wide = half or (precision == "f32" and nbytes >= 4 * CACHE)
+    most, per = (160, 2048) if half else ((110, 1920) if wide else (80, 960))
+    rounds = 1
+    while lowest(nx, ny, 60, rounds * per) > most:
+        rounds += 1
+    w, h = 512 if wide else 256, lowest(nx, ny, 60, rounds * per)
+    if precision == "f64" and h <= 20:
+        w, h = 192, lowest(nx, ny, 60, 768)
+    return (64 if strips(nx, 60) < 4 else w), h
+
+
+def two_steps(nx, ny, precision):
+    h = lowest(nx, ny, 54, SIMDS)
+    h = lowest(nx, ny, 54, 2 * SIMDS) if h > 12 else h
+    t = strips(nx, 54) * -(-ny // h)
+    if strips(nx, 54) < 4 or SIMDS // 4 < t <= SIMDS:
+        return 64, h
+    return (256 if t <= SIMDS else 512 if precision == "f32" else 64), h
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32", "f16mix", "bf16", "f16"])
+@pytest.mark.parametrize("tau", [1.0, 1.3])
+def test_default_shapes(precision, tau):
+    rng = random.Random(7)
+    sizes = [(1, 1), (2, 3), (60, 9), (61, 10), (240, 1), (241, 2), (54, 4000), (4096, 4096), (4096, 2), (170, 9000)]
+    sizes += [(int(2 ** rng.uniform(3, 12)), int(2 ** rng.uniform(3, 12))) for _ in range(60)]
+    seen = set()
+    for nx, ny in sizes:
+        n = rng.randint(1, 4)
+        film = inputs.film_params(n, nx, ny, gamma=[1e-2] * n, mu=[2e-3] * n, hstar=0.1, tau=tau)
+        w, h, nbytes = default_launch(film, precision)
+        want = one_step(nx, ny, precision, nbytes)
+        if tau == 1.0 and precision != "f64":
+            least = 6 if precision == "f32" else 16
+            two = two_steps(nx, ny, precision)
+            # too short for two steps: single ones, in segments that stay so
+            want = two if two[1] >= least else (want[0], min(want[1], least - 2))
+        assert (w, h) == want, (n, nx, ny)
+        seen.add((w, h))
+    assert len(seen) >= 5  # several branches and heights were met
