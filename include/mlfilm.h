@@ -365,7 +365,9 @@ mlf_status mlf_batch_step_until(mlf_batch* b, int64_t max_steps, int32_t check_e
  * >= 1 rows (clamped to each film's ny), persistent != 0: as many
  * workgroups as fit the device at once, each taking work items in turn;
  * 0: one workgroup per item.  0 for block_w or seg_h selects a default by
- * the films' sizes.
+ * the films' sizes, for launches of two steps and of one separately (as for
+ * one film); mlf_batch_get_launch returns that of two where the batch takes
+ * them.
  * EINVAL if the work list would exceed its scratch area. */
 mlf_status mlf_batch_set_launch(mlf_batch* b, int32_t block_w, int32_t seg_h, int32_t persistent);
 mlf_status mlf_batch_get_launch(const mlf_batch* b, int32_t* block_w, int32_t* seg_h, int32_t* persistent);
@@ -390,7 +392,8 @@ mlf_status mlf_batch_get_rounding(const mlf_batch* b, int32_t* mode);
 
 /* Autotuner over block_w x seg_h x persistent, `reps` timed launches each
  * from the current buffer into the other (state unchanged); keeps the
- * fastest per step.  Drops a captured graph.  Synchronises. */
+ * fastest per step (for two steps per launch without changing the shape of
+ * single steps).  Drops a captured graph.  Synchronises. */
 mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int32_t* seg_h, int32_t* persistent);
 
 /* Steps the batch has taken since it was created (-1 for NULL). */

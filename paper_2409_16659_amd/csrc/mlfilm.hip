@@ -1398,8 +1398,9 @@ mlf_status mlf_set_launch(mlf_handle* h, int32_t block_w, int32_t seg_h) {
 
 mlf_status mlf_get_launch(const mlf_handle* h, int32_t* block_w, int32_t* seg_h) {
   if (!h) return MLF_EINVAL;
-  if (block_w) *block_w = h->two.w;
-  if (seg_h) *seg_h = h->two.h;
+  const Shape& s = launch_steps(h, 2) == 2 ? h->two : h->one;
+  if (block_w) *block_w = s.w;
+  if (seg_h) *seg_h = s.h;
   return MLF_OK;
 }
 
@@ -1958,12 +1959,12 @@ namespace {
 
 constexpr int kMaxFilms = 4096;
 constexpr size_t kBatchFlagOff = (kScratchBytes + 255) / 256 * 256;        // int flags[kMaxFilms]
-constexpr size_t kBatchTableOff = kBatchFlagOff + kMaxFilms * sizeof(int);  // BatchFilm<C>[n]
+constexpr size_t kBatchTableOff = kBatchFlagOff + kMaxFilms * sizeof(int);  // BatchFilm<C>[n] per plan
 constexpr size_t kBatchTableBytes = 4u << 20;
-constexpr size_t kBatchItemOff = kBatchTableOff + kBatchTableBytes;         // int2[n_items]
+constexpr size_t kBatchItemOff = kBatchTableOff + 2 * kBatchTableBytes;     // int2[n_items] per plan
 constexpr long long kMaxTileUnits = (12u << 20) / sizeof(int2);  // largest launch accepted (batch_shape_ok)
 constexpr size_t kBatchItemBytes = 24u << 20;
-constexpr size_t kBatchSumOff = kBatchItemOff + kBatchItemBytes;          // double sums[kMaxFilms][4]
+constexpr size_t kBatchSumOff = kBatchItemOff + 2 * kBatchItemBytes;      // double sums[kMaxFilms][4]
 constexpr size_t kBatchMinTabOff = kBatchSumOff + kMaxFilms * kMaxLayers * sizeof(double);  // MinFilm[n]
 constexpr size_t kBatchMinPartOff = kBatchMinTabOff + (kMaxFilms * sizeof(MinFilm) + 255) / 256 * 256;
 constexpr size_t kBatchScratchBytes =
@@ -1972,6 +1973,14 @@ constexpr size_t kBatchScratchBytes =
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 }  // namespace
+
+// Launches of a batch that take one step, or two: their shape, and the device
+// table and work list cut for it.
+struct BatchPlan {
+  Shape shape;
+  int n_items;
+  bool dirty;  // table and list are to be uploaded before the next launch
+};
 
 struct mlf_batch {
   int n;
@@ -1984,11 +1993,10 @@ struct mlf_batch {
   int cur;
   unsigned char* scratch;
   hipStream_t stream;
-  int block_w, seg_h, persistent;
+  BatchPlan plan[2];  // of launches of one step, of two (whose segments decide on them)
+  int persistent;
   int ahead;  // rows in flight asked for (mlf_batch_set_prefetch; no effect on the kernel)
   int max_nl;
-  int n_items;
-  bool table_dirty;
   hipGraphExec_t graph[2];  // as mlf_handle's
   int graph_steps;
   int64_t steps;
@@ -2050,48 +2058,26 @@ size_t batch_table_entry(const mlf_batch* b) {
 }
 
 int* batch_flags(mlf_batch* b) { return reinterpret_cast<int*>(b->scratch + kBatchFlagOff); }
-
-// Steps of the batch's launches, and so of its strips, with segments of `sh`
-// rows (a step left over runs on the same strips).
-int batch_steps(const mlf_batch* b, int sh) {
-  return fusable(b->p0) && !b->film[0]->sr && sh >= min_fused_rows(b->p0) ? 2 : 1;
+unsigned char* batch_table(const mlf_batch* b, int steps) {
+  return b->scratch + kBatchTableOff + (steps - 1) * kBatchTableBytes;
+}
+unsigned char* batch_item_list(const mlf_batch* b, int steps) {
+  return b->scratch + kBatchItemOff + (steps - 1) * kBatchItemBytes;
 }
 
-// Work items (workgroups) of film f under the batch's launch shape.
-long long film_tiles(const mlf_batch* b, int f, int bw, int sh) {
+// Steps of the next launch of the batch (as launch_steps for one film).
+int batch_launch_steps(const mlf_batch* b, int64_t left) {
+  return left >= 2 && fusable(b->p0) && !b->film[0]->sr && b->plan[1].shape.h >= min_fused_rows(b->p0) ? 2 : 1;
+}
+
+// The launch shape that the batch reports: that of two steps where it takes them.
+const Shape& batch_shape(const mlf_batch* b) { return b->plan[batch_launch_steps(b, 2) - 1].shape; }
+
+// Work items (workgroups) of film f in launches of `steps` steps.
+long long film_items(const mlf_batch* b, int f, Shape shape, int steps) {
   const mlf_params& p = b->film[f]->p;
-  const int s = std::min(sh, p.ny);
-  const int nw = bw / 64;
-  return (film_tiles(p, s, batch_steps(b, sh)) + nw - 1) / nw;
-}
-
-long long batch_items(const mlf_batch* b, int bw, int sh) {
-  long long t = 0;
-  for (int f = 0; f < b->n; ++f) t += film_tiles(b, f, bw, sh);
-  return t;
-}
-
-// Default launch shape of a batch: one tile per workgroup (films of uneven
-// sizes and layer counts give uneven tiles, which the device then deals out
-// one by one: 35 films, FP32, 36 rows, 115 us per step, 181 with four), and
-// segments with which the films' tiles together fill the device as one
-// film's do.  FP64 tiles are long (one wavefront per SIMD), so theirs stay at
-// 32 rows or less: 35 films 395 us per step with the read-out, 624 with 68
-// rows and four tiles per workgroup.
-int batch_default_seg(const mlf_batch* b) {
-  int ny = 1;
-  for (const mlf_handle* h : b->film) ny = std::max(ny, h->p.ny);
-  auto seg = [&](int steps) {
-    auto tiles = [&](int s) {
-      long long t = 0;
-      for (const mlf_handle* h : b->film) t += film_tiles(h->p, s, steps);
-      return t;
-    };
-    return steps == 2 ? two_step_seg(tiles, ny) : lowest_seg(tiles, ny, kSimds);
-  };
-  const int sh = seg(fusable(b->p0) ? 2 : 1);
-  if (fusable(b->p0) && sh < min_fused_rows(b->p0)) return std::min(seg(1), min_fused_rows(b->p0) - 2);
-  return b->p0.precision == MLF_F64 ? std::min(sh, 32) : sh;
+  const int nw = shape.w / 64;
+  return (film_tiles(p, std::min(shape.h, p.ny), steps) + nw - 1) / nw;
 }
 
 // Whether a launch shape is accepted: its tiles, counted as one per bw - 4
@@ -2108,69 +2094,135 @@ bool batch_shape_ok(const mlf_batch* b, int bw, int sh) {
   return t <= kMaxTileUnits;
 }
 
-// The widest workgroup where the work list has no room for one tile each.
-int batch_default_w(const mlf_batch* b, int sh) { return batch_shape_ok(b, 64, sh) ? 64 : 256; }
+// Widens a default workgroup where the work list has no room for one tile each.
+void batch_fit(const mlf_batch* b, Shape* s) {
+  if (!batch_shape_ok(b, s->w, s->h)) s->w = 256;
+}
 
-// Device table and work list for the current launch shape (synchronous).
+// Default launch shapes of a batch, of two steps and of one: segments with
+// which the films' tiles together fill the device as one film's do, and one
+// tile per workgroup (films of uneven sizes and layer counts give uneven
+// tiles, which the device then deals out one by one: 35 films, FP32, 36 rows,
+// two steps, 115 us per step, 181 with four).  Single steps of films beyond the
+// Infinity Cache take four strips per workgroup where eight or more lie side by
+// side: FP64, two films of 1024^2, 3 layers, 207 us at 256 x 40, 217 at 256 x
+// 20, 211 at 64 x 80; 24 films of up to 512^2 267 / 415 at 64 / 256 x 44.  Their
+// segments are at most 56 rows high, in whole rounds (one wavefront per SIMD,
+// two with 16-bit storage): FP64, 2000^2, 2 layers, 270 us at 36 rows (one
+// round), 311 at 32.
+void batch_default_launch(const mlf_batch* b, Shape* two, Shape* one) {
+  int ny = 1;
+  long long rows = 0, strips = 0;  // strips weighted by a film's rows and layers
+  size_t bytes = 0;
+  for (const mlf_handle* h : b->film) {
+    const mlf_params& p = h->p;
+    ny = std::max(ny, p.ny);
+    bytes += 2 * h->pop_bytes;
+    rows += (long long)p.n_layers * p.ny;
+    strips += (long long)p.n_layers * p.ny * mlf::strip_count(p.nx, 1);
+  }
+  one->w = bytes > kInfinityCache && strips >= 8 * rows ? 256 : 64;
+  two->w = 64;
+  // tiles, counting the lanes that a film's last workgroup leaves idle
+  auto tiles = [b](const Shape* s, int steps) {
+    return [b, nw = s->w / 64, steps](int h) {
+      long long t = 0;
+      for (const mlf_handle* f : b->film)
+        t += (film_tiles(f->p, std::min(h, f->p.ny), steps) + nw - 1) / nw * nw;
+      return t;
+    };
+  };
+  const bool half = b->p0.precision != MLF_F32 && b->p0.precision != MLF_F64;
+  const long long round = half ? 2 * kSimds : kSimds;
+  one->h = lowest_seg(tiles(one, 1), ny, (tiles(one, 1)(56) + round - 1) / round * round);
+  if (fusable(b->p0)) two->h = two_step_seg(tiles(two, 2), ny);
+  if (fusable(b->p0) && two->h < min_fused_rows(b->p0)) one->h = std::min(one->h, min_fused_rows(b->p0) - 2);
+  if (!fusable(b->p0) || two->h < min_fused_rows(b->p0)) *two = *one;
+  batch_fit(b, two);
+  batch_fit(b, one);
+}
+
+void set_batch_shapes(mlf_batch* b, Shape two, Shape one) {
+  b->plan[0] = {one, 0, true};
+  b->plan[1] = {two, 0, true};
+}
+
+// Device table and work list of the launches of `steps` steps (synchronous).
 template <typename C>
-mlf_status upload_table_t(mlf_batch* b) {
+mlf_status upload_plan_t(mlf_batch* b, int steps) {
+  BatchPlan& plan = b->plan[steps - 1];
+  const int nw = plan.shape.w / 64, halo = 2 * mlf::march_halo(steps);
   std::vector<mlf::BatchFilm<C>> tab(b->n);
-  std::vector<int2> items;
-  items.reserve((size_t)b->n_items);
   for (int f = 0; f < b->n; ++f) {
     mlf_handle* h = b->film[f];
     std::memset(&tab[f], 0, sizeof(tab[f]));
-    tab[f].kc = make_consts<C>(h, Shape{b->block_w, std::min(b->seg_h, h->p.ny)}, batch_steps(b, b->seg_h));
+    tab[f].kc = make_consts<C>(h, Shape{plan.shape.w, std::min(plan.shape.h, h->p.ny)}, steps);
     tab[f].kc.flag = batch_flags(b) + f;
     tab[f].offset = (long long)b->offset[f];
     tab[f].nl = h->p.n_layers;
   }
-  // longest items first (layers x rows marched; the last segment of a film may
-  // be short), so that the end of a launch is made of short ones
-  std::vector<std::pair<int, int2>> cost;
-  const int nw = b->block_w / 64, halo = 2 * mlf::march_halo(batch_steps(b, b->seg_h));
+  // longest items first (layers x rows marched; a film's last segment may be
+  // short), so that the end of a launch is made of short ones; a film's items
+  // are two runs of equal ones
+  struct Run {
+    int cost, film, from, to;
+  };
+  std::vector<Run> runs;
+  size_t n_items = 0;
   for (int f : b->order) {
     const mlf::StepConsts<C>& k = tab[f].kc;
-    const int nt = (int)film_tiles(b, f, b->block_w, b->seg_h);
-    for (int t = 0; t < nt; ++t) {
-      const int seg = t * nw / k.nstrip;
-      cost.emplace_back(tab[f].nl * (std::min(k.seg_h, k.ny - seg * k.seg_h) + halo), make_int2(f, t));
-    }
+    const int nt = (int)film_items(b, f, plan.shape, steps);
+    const int last = ((k.nseg - 1) * k.nstrip + nw - 1) / nw;  // first item that begins in the last segment
+    if (last > 0) runs.push_back({tab[f].nl * (k.seg_h + halo), f, 0, last});
+    if (last < nt) runs.push_back({tab[f].nl * (k.ny - (k.nseg - 1) * k.seg_h + halo), f, last, nt});
+    n_items += (size_t)nt;
   }
-  std::stable_sort(cost.begin(), cost.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-  for (const auto& c : cost) items.push_back(c.second);
-  BHIPCHK(hipMemcpyAsync(b->scratch + kBatchTableOff, tab.data(), tab.size() * sizeof(tab[0]),
-                         hipMemcpyHostToDevice, b->stream));
-  BHIPCHK(hipMemcpyAsync(b->scratch + kBatchItemOff, items.data(), items.size() * sizeof(int2),
-                         hipMemcpyHostToDevice, b->stream));
+  std::stable_sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.cost > y.cost; });
+  std::vector<int2> items;
+  items.reserve(n_items);
+  for (const Run& r : runs)
+    for (int t = r.from; t < r.to; ++t) items.push_back(make_int2(r.film, t));
+  BHIPCHK(hipMemcpyAsync(batch_table(b, steps), tab.data(), tab.size() * sizeof(tab[0]), hipMemcpyHostToDevice,
+                         b->stream));
+  BHIPCHK(hipMemcpyAsync(batch_item_list(b, steps), items.data(), items.size() * sizeof(int2), hipMemcpyHostToDevice,
+                         b->stream));
   BHIPCHK(hipStreamSynchronize(b->stream));
-  b->n_items = (int)items.size();
-  b->table_dirty = false;
+  plan.n_items = (int)items.size();
+  plan.dirty = false;
   return MLF_OK;
 }
 
-mlf_status upload_table(mlf_batch* b) {
-  b->n_items = (int)batch_items(b, b->block_w, b->seg_h);
-  return batch_double(b) ? upload_table_t<double>(b) : upload_table_t<float>(b);
+// Uploads what launches of `steps` steps read, if it is not up to date.
+mlf_status batch_upload(mlf_batch* b, int steps) {
+  if (!b->plan[steps - 1].dirty) return MLF_OK;
+  return batch_double(b) ? upload_plan_t<double>(b, steps) : upload_plan_t<float>(b, steps);
+}
+
+// What a graph's launches may read.
+mlf_status batch_upload_all(mlf_batch* b) {
+  const mlf_status st = batch_upload(b, 1);
+  return st == MLF_OK && batch_launch_steps(b, 2) == 2 ? batch_upload(b, 2) : st;
 }
 
 template <typename R, typename S, typename C, bool T1, int EA, int EB, int STEPS>
 hipError_t launch_batch_st(const mlf_batch* b, int flip) {
   auto kern = mlf::batch_kernel<R, S, C, T1, EA, EB, STEPS>;
-  const size_t lds = b->block_w / 64 * mlf::march_lds<C>(kMaxLayers, STEPS);
-  int grid = (b->n_items + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
+  const BatchPlan& plan = b->plan[STEPS - 1];
+  const int block_w = plan.shape.w;
+  const size_t lds = block_w / 64 * mlf::march_lds<C>(kMaxLayers, STEPS);
+  int grid = (plan.n_items + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
   if (b->persistent) {
     int nb = 0, dev = 0, ncu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, b->block_w, lds);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, block_w, lds);
     if (e != hipSuccess) return e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
     const int slots = std::max(1, nb) * std::max(1, ncu) / mlf::kXcds * mlf::kXcds;
     grid = std::max(mlf::kXcds, std::min(grid, slots));
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)b->block_w), lds, b->stream,
-                     reinterpret_cast<const mlf::BatchFilm<C>*>(b->scratch + kBatchTableOff),
-                     reinterpret_cast<const int2*>(b->scratch + kBatchItemOff), b->n_items, b->pop[0], b->pop[1],
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)block_w), lds, b->stream,
+                     reinterpret_cast<const mlf::BatchFilm<C>*>(batch_table(b, STEPS)),
+                     reinterpret_cast<const int2*>(batch_item_list(b, STEPS)), plan.n_items, b->pop[0], b->pop[1],
                      flip, (uint32_t)b->steps);
   return hipGetLastError();
 }
@@ -2202,7 +2254,7 @@ hipError_t d1_batch_launch_t(const mlf_batch* b, int steps) {
     threads = std::max(threads, d1_threads(h->p.nx));
   }
   hipLaunchKernelGGL((mlf::d1q3_resident_batch<C, T1, EA, EB>), dim3((unsigned)b->n), dim3((unsigned)threads), lds,
-                     b->stream, reinterpret_cast<const mlf::BatchFilm<C>*>(b->scratch + kBatchTableOff), b->pop[0],
+                     b->stream, reinterpret_cast<const mlf::BatchFilm<C>*>(batch_table(b, 1)), b->pop[0],
                      b->pop[1], b->cur, steps);
   return hipGetLastError();
 }
@@ -2219,11 +2271,6 @@ hipError_t d1_batch_launch_c(const mlf_batch* b, int steps) {
 
 hipError_t d1_batch_launch(const mlf_batch* b, int steps) {
   return b->p0.precision == MLF_F64 ? d1_batch_launch_c<double>(b, steps) : d1_batch_launch_c<float>(b, steps);
-}
-
-// Steps of the next launch of the batch (as launch_steps for one film).
-int batch_launch_steps(const mlf_batch* b, int64_t left) {
-  return left >= 2 ? batch_steps(b, b->seg_h) : 1;
 }
 
 // `steps` steps of every film from buffer `flip` into the other one.
@@ -2249,7 +2296,6 @@ void drop_graph(mlf_batch* b) {
 mlf_status batch_ready(mlf_batch* b) {
   for (int f = 0; f < b->n; ++f)
     if (!b->ready[f]) return bfail(b, MLF_EINVAL, "film " + std::to_string(f) + " is not initialised");
-  if (b->table_dirty) return upload_table(b);
   return MLF_OK;
 }
 
@@ -2327,8 +2373,9 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
     auto lu = [&](int f) { return (long long)films[f].n_layers * films[f].nx * films[f].ny; };
     return lu(a) > lu(c);
   });
-  b->seg_h = batch_default_seg(b);
-  b->block_w = batch_default_w(b, b->seg_h);
+  Shape two, one;
+  batch_default_launch(b, &two, &one);
+  set_batch_shapes(b, two, one);
   b->persistent = 0;
   b->ahead = 1;
   if (!batch_shape_ok(b, 256, 8) ||
@@ -2337,7 +2384,6 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
     delete b;
     return MLF_EUNSUPPORTED;
   }
-  b->table_dirty = true;
   b->graph[0] = b->graph[1] = nullptr;
   b->graph_steps = 0;
   b->steps = 0;
@@ -2358,7 +2404,7 @@ mlf_status mlf_batch_init(mlf_batch* b, int32_t film, const double* hgt, const d
   BHIPCHK(hipMemsetAsync(batch_flags(b) + film, 0, sizeof(int), b->stream));
   BHIPCHK(hipStreamSynchronize(b->stream));
   b->ready[film] = true;
-  b->table_dirty = true;  // reference heights and scales changed
+  b->plan[0].dirty = b->plan[1].dirty = true;  // reference heights and scales changed
   return MLF_OK;
 }
 
@@ -2374,7 +2420,7 @@ mlf_status mlf_batch_init_device(mlf_batch* b, int32_t film, const double* hgt, 
   BHIPCHK(hipMemsetAsync(batch_flags(b) + film, 0, sizeof(int), b->stream));
   BHIPCHK(hipStreamSynchronize(b->stream));
   b->ready[film] = true;
-  b->table_dirty = true;
+  b->plan[0].dirty = b->plan[1].dirty = true;
   return MLF_OK;
 }
 
@@ -2431,7 +2477,7 @@ mlf_status mlf_batch_init_device_all_u(mlf_batch* b, const double* const* hgts, 
     b->film[f]->initialised = true;
     b->ready[f] = true;
   }
-  b->table_dirty = true;
+  b->plan[0].dirty = b->plan[1].dirty = true;
   return MLF_OK;
 }
 
@@ -2459,6 +2505,7 @@ mlf_status mlf_batch_step(mlf_batch* b, int64_t nsteps) {
   if (st != MLF_OK) return st;
   b->failed = -1;
   if (b->p0.lattice == MLF_D1Q3) {
+    if ((st = batch_upload(b, 1)) != MLF_OK) return st;
     for (int64_t left = nsteps; left > 0;) {
       const int chunk = (int)std::min<int64_t>(left, kD1MaxStepsPerLaunch);
       BHIPCHK(d1_batch_launch(b, chunk));
@@ -2468,6 +2515,7 @@ mlf_status mlf_batch_step(mlf_batch* b, int64_t nsteps) {
     }
     return batch_guard(b);
   }
+  if (b->graph_steps && (st = batch_upload_all(b)) != MLF_OK) return st;
   st = mlf::advance(
       nsteps, 0, b->graph_steps, [&](int64_t room) { return batch_launch_steps(b, room); },
       [&]() {
@@ -2476,6 +2524,8 @@ mlf_status mlf_batch_step(mlf_batch* b, int64_t nsteps) {
         return MLF_OK;
       },
       [&](int adv) {
+        const mlf_status up = batch_upload(b, adv);
+        if (up != MLF_OK) return up;
         BHIPCHK(launch_batch(b, b->cur, adv));
         b->cur ^= 1;
         b->steps += adv;
@@ -2497,6 +2547,7 @@ mlf_status mlf_batch_capture(mlf_batch* b, int32_t steps) {
   if (!b->film.empty() && b->film[0]->sr)
     return bfail(b, MLF_EUNSUPPORTED, "stochastic rounding draws from the step count, which a graph would freeze");
   mlf_status st = batch_ready(b);
+  if (st == MLF_OK) st = batch_upload_all(b);
   if (st != MLF_OK) return st;
   for (int c = 0; c < 2; ++c) {
     const hipError_t e = capture_steps(
@@ -2616,16 +2667,20 @@ mlf_status mlf_batch_step_until(mlf_batch* b, int64_t max_steps, int32_t check_e
 
 mlf_status mlf_batch_set_launch(mlf_batch* b, int32_t block_w, int32_t seg_h, int32_t persistent) {
   if (!b) return MLF_EINVAL;
-  const int sh = seg_h == 0 ? batch_default_seg(b) : seg_h, bw = block_w == 0 ? batch_default_w(b, sh) : block_w;
-  if (bw != 64 && bw != 128 && bw != 192 && bw != 256)
+  if (block_w != 0 && block_w != 64 && block_w != 128 && block_w != 192 && block_w != 256)
     return bfail(b, MLF_EINVAL, "block_w must be 64, 128, 192 or 256");
-  if (sh < 1) return bfail(b, MLF_EINVAL, "seg_h must be >= 1");
-  if (!batch_shape_ok(b, block_w == 0 ? 256 : bw, seg_h == 0 ? 8 : sh))
+  if (seg_h < 0) return bfail(b, MLF_EINVAL, "seg_h must be >= 1");
+  if (!batch_shape_ok(b, block_w == 0 ? 256 : block_w, seg_h == 0 ? 8 : seg_h))
     return bfail(b, MLF_EINVAL, "launch shape gives too many work items");
-  b->block_w = bw;
-  b->seg_h = sh;
+  Shape two, one;
+  batch_default_launch(b, &two, &one);
+  for (Shape* s : {&two, &one}) {
+    if (seg_h != 0) s->h = seg_h;
+    if (block_w != 0) s->w = block_w;
+    else batch_fit(b, s);
+  }
+  set_batch_shapes(b, two, one);
   b->persistent = persistent != 0;
-  b->table_dirty = true;
   drop_graph(b);
   return MLF_OK;
 }
@@ -2655,7 +2710,7 @@ mlf_status mlf_batch_set_rounding(mlf_batch* b, int32_t mode) {
     return bfail(b, MLF_EINVAL, "stochastic rounding needs D2Q9 films with MLF_F16 or MLF_BF16 storage");
   drop_graph(b);
   for (mlf_handle* h : b->film) h->sr = mode == MLF_ROUND_STOCHASTIC_REST;
-  b->table_dirty = true;
+  b->plan[0].dirty = b->plan[1].dirty = true;
   return MLF_OK;
 }
 
@@ -2667,8 +2722,8 @@ mlf_status mlf_batch_get_rounding(const mlf_batch* b, int32_t* mode) {
 
 mlf_status mlf_batch_get_launch(const mlf_batch* b, int32_t* block_w, int32_t* seg_h, int32_t* persistent) {
   if (!b) return MLF_EINVAL;
-  if (block_w) *block_w = b->block_w;
-  if (seg_h) *seg_h = b->seg_h;
+  if (block_w) *block_w = batch_shape(b).w;
+  if (seg_h) *seg_h = batch_shape(b).h;
   if (persistent) *persistent = b->persistent;
   return MLF_OK;
 }
@@ -2678,13 +2733,14 @@ mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int3
   mlf_status st = batch_ready(b);
   if (st != MLF_OK) return st;
   if (b->p0.lattice == MLF_D1Q3) {  // fixed shape: one workgroup per film
-    if (block_w) *block_w = b->block_w;
-    if (seg_h) *seg_h = b->seg_h;
+    if (block_w) *block_w = batch_shape(b).w;
+    if (seg_h) *seg_h = batch_shape(b).h;
     if (persistent) *persistent = b->persistent;
     return MLF_OK;
   }
   drop_graph(b);
-  const int keep_w = b->block_w, keep_h = b->seg_h, keep_p = b->persistent;
+  const Shape keep_two = b->plan[1].shape, keep_one = b->plan[0].shape;
+  const int keep_p = b->persistent;
   struct Cand {
     int w, h, p;
   };
@@ -2697,13 +2753,12 @@ mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int3
   BHIPCHK(hipEventCreate(&e0));
   BHIPCHK(hipEventCreate(&e1));
   float best = 1e30f;
-  Cand pick{keep_w, keep_h, keep_p};
+  Cand pick{keep_two.w, keep_two.h, keep_p};
   for (const Cand& c : cand) {
-    b->block_w = c.w;
-    b->seg_h = c.h;
+    set_batch_shapes(b, {c.w, c.h}, {c.w, c.h});
     b->persistent = c.p;
-    if ((st = upload_table(b)) != MLF_OK) break;
     const int adv = batch_launch_steps(b, 2);
+    if ((st = batch_upload(b, adv)) != MLF_OK) break;
     // current -> other buffer, never swapped: the state is left unchanged
     if ((st = bhip(b, launch_batch(b, b->cur, adv), "autotune launch")) != MLF_OK) break;
     if ((st = bhip(b, hipEventRecord(e0, b->stream), "hipEventRecord")) != MLF_OK) break;
@@ -2721,18 +2776,15 @@ mlf_status mlf_batch_autotune(mlf_batch* b, int32_t reps, int32_t* block_w, int3
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st == MLF_OK) {
-    b->block_w = pick.w;
-    b->seg_h = pick.h;
+    set_batch_shapes(b, {pick.w, pick.h}, {pick.w, pick.h});
     b->persistent = pick.p;
+    // a shape tuned for two steps leaves that of a step left over as it was
+    if (batch_launch_steps(b, 2) == 2) b->plan[0].shape = keep_one;
   } else {
-    b->block_w = keep_w;
-    b->seg_h = keep_h;
+    set_batch_shapes(b, keep_two, keep_one);
     b->persistent = keep_p;
   }
-  b->table_dirty = true;
-  mlf_status up = upload_table(b);
   if (st != MLF_OK) return st;
-  if (up != MLF_OK) return up;
   if (block_w) *block_w = pick.w;
   if (seg_h) *seg_h = pick.h;
   if (persistent) *persistent = pick.p;
