@@ -210,10 +210,12 @@ def _find(dirname, suffix):
 
 
 def _step_rows(rows, grid, per, warmup, steps, grid_key):
-    """The dispatches of the last `steps` steps, `per` steps each (the
-    kernel's last template argument)."""
-    sel = [r for r in rows if "step_kernel" in r["Kernel_Name"] and int(r[grid_key]) == grid
-           and (f", {per}>" in r["Kernel_Name"] or f"ELi{per}EEE" in r["Kernel_Name"])]
+    """The dispatches of the last `steps` steps, `per` steps each (the last
+    template argument but one of the kernel)."""
+    import re
+
+    mine = re.compile(rf"step_kernel<.*, {per}, \d+>|step_kernelI.*ELi{per}ELi\d+EEE")
+    sel = [r for r in rows if mine.search(r["Kernel_Name"]) and int(r[grid_key]) == grid]
     sel.sort(key=lambda r: int(r["Dispatch_Id"]) if "Dispatch_Id" in r else int(r["Start_Timestamp"]))
     if len(sel) < warmup // per + steps // per:
         raise ValueError(f"expected {warmup // per + steps // per} dispatches of grid {grid}, found {len(sel)}")

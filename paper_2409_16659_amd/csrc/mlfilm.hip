@@ -759,6 +759,8 @@ constexpr size_t kInfinityCache = 256u << 20;
 // storage, whose rows load half as much): 777 x 515, 3 layers, FP64 (8 rows)
 // 37.1 us per step with one wavefront per workgroup, 38.0 with four; f16mix, 2
 // layers, 2989 x 444 26.1 us with two per SIMD (12 rows), 30.6 with one (24).
+// (With fewer tiles than CUs it makes no difference to speak of, up to 4 %:
+// those films report four wavefronts per workgroup, as two-step ones do.)
 // Films that stream from HBM take four strips side by side in a workgroup,
 // which share the columns that both read, and segments of at most 80 rows in
 // whole rounds of workgroups: FP64, 4 layers, 2596 x 1399 455 us at 32 rows (two
@@ -775,13 +777,17 @@ Shape one_step_shape(const mlf_params& p) {
   const bool half = p.precision != MLF_F64 && p.precision != MLF_F32;
   const size_t bytes = 2 * buffer_bytes(p.precision, p.n_layers, (size_t)pitch_of(&p) * p.ny, nq_of(&p));
   auto tiles = [&](int h) { return film_tiles(p, h, 1); };
-  if (bytes <= kInfinityCache) return {64, lowest_seg(tiles, p.ny, half ? 2 * kSimds : kSimds)};
+  const bool narrow = mlf::strip_count(p.nx, 1) < 4;  // too few strips to share anything
+  if (bytes <= kInfinityCache) {
+    const int h = lowest_seg(tiles, p.ny, half ? 2 * kSimds : kSimds);
+    return {!narrow && tiles(h) <= kSimds / 4 ? 256 : 64, h};
+  }
   const bool wide = half || (p.precision == MLF_F32 && bytes >= 4 * kInfinityCache);
   const int most = half ? 160 : wide ? 110 : 80;
   const long long round = half ? 2 * kSimds : (wide ? 2 : 1) * kSimds * 15 / 16;
   Shape s{wide ? 512 : 256, lowest_seg(tiles, p.ny, (tiles(most) + round - 1) / round * round)};
   if (p.precision == MLF_F64 && s.h <= 20) s = {192, lowest_seg(tiles, p.ny, kSimds * 3 / 4)};
-  if (mlf::strip_count(p.nx, 1) < 4) s.w = 64;  // too few strips to share anything
+  if (narrow) s.w = 64;
   return s;
 }
 

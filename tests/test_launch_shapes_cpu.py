@@ -38,7 +38,8 @@ def lowest(nx, ny, cols, most):
 def one_step(nx, ny, precision, nbytes):
     half = precision not in ("f64", "f32")
     if nbytes <= CACHE:
-        return 64, lowest(nx, ny, 60, (2 if half else 1) * SIMDS)
+        h = lowest(nx, ny, 60, (2 if half else 1) * SIMDS)
+        return (256 if strips(nx, 60) >= 4 and strips(nx, 60) * -(-ny // h) <= SIMDS // 4 else 64), h
     wide = half or (precision == "f32" and nbytes >= 4 * CACHE)
     most, per = (160, 2048) if half else ((110, 1920) if wide else (80, 960))
     rounds = 1
