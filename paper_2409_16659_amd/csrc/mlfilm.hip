@@ -860,10 +860,11 @@ hipError_t launch_st(const mlf_handle* h, const void* src, void* dst) {
   // grid padded to a multiple of the XCD count (tile_of_block)
   const int ngroups = (kc.nstrip * kc.nseg + (int)nw - 1) / (int)nw;
   const int nblocks = (ngroups + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
-  if constexpr (std::is_same_v<R, C> && std::is_same_v<S, C>)
+  if constexpr (STEPS == 1)  // films of one row have segments too short for two
     if (h->p.ny == 1) {
-      hipLaunchKernelGGL((mlf::row_step_kernel<C, NL, T1, EA, EB, STEPS>), dim3((unsigned)ngroups),
-                         dim3((unsigned)shape.w), 0, h->stream, static_cast<const C*>(src), static_cast<C*>(dst), kc);
+      hipLaunchKernelGGL((mlf::row_step_kernel<R, S, C, NL, T1, EA, EB>), dim3((unsigned)ngroups),
+                         dim3((unsigned)shape.w), 0, h->stream, static_cast<const unsigned char*>(src),
+                         static_cast<unsigned char*>(dst), kc);
       return hipGetLastError();
     }
   auto launch = [&](auto kern) {
