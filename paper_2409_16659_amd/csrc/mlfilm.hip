@@ -852,6 +852,15 @@ mlf::StepConsts<C> make_consts(const mlf_handle* h, Shape shape, int steps) {
   return k;
 }
 
+// Lets a kernel launch with `lds` bytes of dynamic LDS (above 64 KiB it has to
+// be asked for).
+template <typename K>
+hipError_t allow_lds(K kern, size_t lds) {
+  if (lds <= 65536) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)lds);
+}
+
 template <typename R, typename S, typename C, int NL, bool T1, int EA, int EB, int STEPS>
 hipError_t launch_st(const mlf_handle* h, const void* src, void* dst) {
   const Shape shape = STEPS == 2 ? h->two : h->one;
@@ -867,14 +876,18 @@ hipError_t launch_st(const mlf_handle* h, const void* src, void* dst) {
                          static_cast<unsigned char*>(dst), kc);
       return hipGetLastError();
     }
+  // up to 160 KiB, all that a CU has, for 512 lanes of four FP32 layers at two steps
+  const size_t lds = nw * mlf::march_lds<C>(NL, STEPS);
   auto launch = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3((unsigned)shape.w), nw * mlf::march_lds<C>(NL, STEPS),
-                       h->stream, static_cast<const unsigned char*>(src), static_cast<unsigned char*>(dst), kc);
+    const hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3((unsigned)shape.w), lds, h->stream,
+                       static_cast<const unsigned char*>(src), static_cast<unsigned char*>(dst), kc);
+    return hipGetLastError();
   };
   constexpr int kNarrow = mlf::step_lanes<C, NL>(256), kWide = mlf::step_lanes<C, NL>(512);
-  if (shape.w <= 256) launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kNarrow>);
-  else launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kWide>);
-  return hipGetLastError();
+  if (shape.w <= 256) return launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kNarrow>);
+  return launch(mlf::step_kernel<R, S, C, NL, T1, EA, EB, STEPS, kWide>);
 }
 
 // `steps` 2 only where fusable(h->p).
@@ -1052,11 +1065,8 @@ hipError_t row_launch_nl(mlf_handle* h, int steps) {
     if (steps < 1 || steps > mlf::kRowTileSteps) return hipErrorInvalidValue;
     const size_t lds = mlf::row_tile_lds<C>(NL);
     auto kern = mlf::d2q9_row_tiled<C, NL, T1, EA, EB>;
-    if (lds > 65536) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
+    const hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
     const int tiles = (p.nx + mlf::kRowTileCore - 1) / mlf::kRowTileCore;
     hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(mlf::kRowTileThreads), lds, h->stream,
                        static_cast<const C*>(h->pop[h->cur]), static_cast<C*>(h->pop[h->cur ^ 1]), kc, steps,
@@ -1066,11 +1076,8 @@ hipError_t row_launch_nl(mlf_handle* h, int steps) {
   }
   const size_t lds = mlf::row_resident_lds<C>(p.nx, NL);
   auto kern = mlf::d2q9_row_resident<C, NL, T1, EA, EB>;
-  if (lds > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e = allow_lds(kern, lds);
+  if (e != hipSuccess) return e;
   const int threads = std::min(mlf::kRowThreads, std::max(64, (p.nx + 63) / 64 * 64));
   hipLaunchKernelGGL(kern, dim3(1), dim3((unsigned)threads), lds, h->stream, static_cast<const C*>(h->pop[h->cur]),
                      static_cast<C*>(h->pop[h->cur ^ 1]), kc, steps);
@@ -2217,6 +2224,8 @@ hipError_t launch_batch_st(const mlf_batch* b, int flip) {
   const BatchPlan& plan = b->plan[STEPS - 1];
   const int block_w = plan.shape.w;
   const size_t lds = block_w / 64 * mlf::march_lds<C>(kMaxLayers, STEPS);
+  const hipError_t allowed = allow_lds(kern, lds);
+  if (allowed != hipSuccess) return allowed;
   int grid = (plan.n_items + mlf::kXcds - 1) / mlf::kXcds * mlf::kXcds;
   if (b->persistent) {
     int nb = 0, dev = 0, ncu = 0;
