@@ -33,6 +33,14 @@ constexpr int kWgSlices = 85;    // slices of the weight gradient (3 x 85 workgr
 
 // ---- elementwise and reduction kernels (FP32) ------------------------------
 
+// Four consecutive values of a caller's image, which is aligned to its
+// elements only: one 16-byte access all the same.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 load4(const float* p) {
+  const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // mean over the grid of each (sample, layer) plane: out[bi] (one block of
 // 1024 threads each; 16-byte loads into four independent partial sums, then
 // a tree in LDS; a fixed order, so the result is reproducible)
@@ -134,8 +142,7 @@ __global__ void __launch_bounds__(256) patch_to_latent(const float* __restrict__
     for (int c = 0; c < 32; ++c) acc[c] = bias ? bias[c0 + c] : 0.f;
     for (int i = 0; i < nl; ++i)
       for (int u = 0; u < kPatch; ++u) {
-        float4 pv = *reinterpret_cast<const float4*>(
-            P + (((long long)b * nl + i) * ny + kPatch * py + u) * nx + kPatch * px);
+        float4 pv = load4(P + (((long long)b * nl + i) * ny + kPatch * py + u) * nx + kPatch * px);
         const float mu = pmean[b * nl + i];
         pv = make_float4((pv.x - mu) * pscale, (pv.y - mu) * pscale, (pv.z - mu) * pscale, (pv.w - mu) * pscale);
         const float ps[4] = {pv.x, pv.y, pv.z, pv.w};
@@ -235,7 +242,7 @@ __global__ void __launch_bounds__(256) patch_to_latent_small(const float* __rest
                                                              int ny, int nx, int C, const float* __restrict__ pmean,
                                                              float pscale) {
   constexpr int J = 16 * NL, RS = 33;
-  __shared__ float sw[J * 32];
+  __shared__ __attribute__((aligned(16))) float sw[J * 32];
   __shared__ float so[64 * RS];
   const int gy = ny / kPatch, gx = nx / kPatch, groups = C / 32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -247,8 +254,7 @@ __global__ void __launch_bounds__(256) patch_to_latent_small(const float* __rest
   for (int i = 0; i < NL; ++i)
 #pragma unroll
     for (int u = 0; u < kPatch; ++u)
-      pv[i][u] = *reinterpret_cast<const float4*>(P + (((long long)b * NL + i) * ny + kPatch * py + u) * nx +
-                                                  kPatch * px);
+      pv[i][u] = load4(P + (((long long)b * NL + i) * ny + kPatch * py + u) * nx + kPatch * px);
   for (int t = threadIdx.x; t < J * 8; t += 256)
     *reinterpret_cast<float4*>(sw + 4 * t) = *reinterpret_cast<const float4*>(W + (long long)(t / 8) * C + c0 + 4 * (t % 8));
   float acc[8];
@@ -526,7 +532,7 @@ __global__ void __launch_bounds__(256) loss_grad(const float* __restrict__ d, co
   float s = 0.f;
   for (long long t = (blockIdx.x * 256LL + threadIdx.x) * 4; t < n_plane; t += (long long)gridDim.x * 1024) {
     const float4 dv = *reinterpret_cast<const float4*>(d + base + t);
-    const float4 a = *reinterpret_cast<const float4*>(h0 + base + t), b = *reinterpret_cast<const float4*>(h1 + base + t);
+    const float4 a = load4(h0 + base + t), b = load4(h1 + base + t);
     float4 g;
     auto one = [&](float dd, float x0, float x1) {
       const float free = dd - mu;
