@@ -520,16 +520,16 @@ __global__ void conv_weights(const float* __restrict__ w, __bf16* __restrict__ w
 
 // Loss and its gradient in one pass over the decoder output d, the plane means
 // that make it mass-free, and the heights: e = (d - mean) - (h1 - h0) inv_s,
-// grad = k e (where given), part[plane][block] = sum e^2.  Grid: (blocks, planes).
-constexpr int kLossBlocks = 16;  // per plane
+// grad = k e (where given), part[plane][block] = sum e^2, in FP64 (the pass is
+// bound by its bytes).  Grid: (loss_blocks(n_plane), planes).
 __global__ void __launch_bounds__(256) loss_grad(const float* __restrict__ d, const float* __restrict__ mean,
                                                  const float* __restrict__ h0, const float* __restrict__ h1,
                                                  float inv_s, float k, float* __restrict__ grad,
-                                                 float* __restrict__ part, long long n_plane) {
-  __shared__ float red[4];
+                                                 double* __restrict__ part, long long n_plane) {
+  __shared__ double red[4];
   const long long base = (long long)blockIdx.y * n_plane;
   const float mu = mean[blockIdx.y];
-  float s = 0.f;
+  double s = 0.0;
   for (long long t = (blockIdx.x * 256LL + threadIdx.x) * 4; t < n_plane; t += (long long)gridDim.x * 1024) {
     const float4 dv = *reinterpret_cast<const float4*>(d + base + t);
     const float4 a = load4(h0 + base + t), b = load4(h1 + base + t);
@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(256) loss_grad(const float* __restrict__ d, co
 }
 
 // out = sum of n partials in FP64, fixed order (one workgroup)
-__global__ void __launch_bounds__(256) loss_finish(const float* __restrict__ part, double* __restrict__ out, int n) {
+__global__ void __launch_bounds__(256) loss_finish(const double* __restrict__ part, double* __restrict__ out, int n) {
   __shared__ double red[4];
   double s = 0.0;
   for (int t = threadIdx.x; t < n; t += 256) s += part[t];
@@ -575,6 +575,9 @@ __global__ void adam(float* __restrict__ p, const float* __restrict__ g, float* 
     p[t] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
   }
 }
+
+// Workgroups of loss_grad per plane: 4096 values each, 16 to 1024 of them.
+int loss_blocks(long long n_plane) { return (int)std::max(16LL, std::min(n_plane / 4096, 1024LL)); }
 
 unsigned grid1(long long n) { return (unsigned)std::max(1LL, std::min((n + 255) / 256, 16384LL)); }
 // per-plane elementwise kernels: blockIdx.y = plane
@@ -656,8 +659,8 @@ struct mlf_nop {
   // workspace regions
   float *par, *grad, *am, *av;
   __bf16 *w1b, *w1t, *w2b, *w2t;  // [L][9][C][C]
-  float *D, *dD, *mean, *mean_h, *loss_part;  // mean: of D, then of dD; mean_h: of the input heights
-  double* loss;
+  float *D, *dD, *mean, *mean_h;  // mean: of D, then of dD; mean_h: of the input heights
+  double *loss_part, *loss;
   float *r, *a, *dr;              // r: [L+1][lat], a: [L][lat], dr: [lat]
   __bf16 *rb, *gb, *cb, *cb2;     // rb: [L+1][lat], gb: [L][lat], cb, cb2: [lat]
   float *part;
@@ -737,7 +740,7 @@ Layout layout_of(const mlf_nop_params* p) {
       a64(L * 9 * C * C) * 2 * 4,                                           // w1b w1t w2b w2t (bf16 each)
       a64(s.img) * 4, a64(s.img) * 4,                                       // D dD
       a64(p->batch * N) * 4, a64(p->batch * N) * 4,                         // mean mean_h
-      a64(p->batch * N * kLossBlocks) * 4, 256,                             // loss_part loss
+      a64(p->batch * N * loss_blocks((long long)p->ny * p->nx)) * 8, 256,   // loss_part loss
       a64((L + 1) * s.lat) * 4, a64(std::max(1LL, L) * s.lat) * 4,          // r a
       a64(s.lat) * 4,                                                       // dr
       a64((L + 1) * s.lat) * 2, a64(std::max(1LL, L) * s.lat) * 2,          // rb gb
@@ -980,9 +983,9 @@ mlf_status forward(mlf_nop* m, int batch, const float* h, bool train) {
 mlf_status loss_and_grad(mlf_nop* m, int batch, const float* h0, const float* h1, bool want_grad) {
   const int planes = batch * m->p.n_layers;
   const long long plane = (long long)m->p.ny * m->p.nx, img = planes * plane;
-  NLAUNCH(loss_grad, dim3(kLossBlocks, planes), dim3(256), 0, m->stream, m->D, m->mean, h0, h1,
+  NLAUNCH(loss_grad, dim3(loss_blocks(plane), planes), dim3(256), 0, m->stream, m->D, m->mean, h0, h1,
           (float)(1.0 / m->p.scale), 2.f / (float)img, want_grad ? m->dD : nullptr, m->loss_part, plane);
-  NLAUNCH(loss_finish, dim3(1), dim3(256), 0, m->stream, m->loss_part, m->loss, planes * kLossBlocks);
+  NLAUNCH(loss_finish, dim3(1), dim3(256), 0, m->stream, m->loss_part, m->loss, planes * loss_blocks(plane));
   return MLF_OK;
 }
 
@@ -1085,7 +1088,7 @@ mlf_status mlf_nop_create(const mlf_nop_params* p, void* workspace, void* stream
   m->dD = reinterpret_cast<float*>(w + s.off[6]);
   m->mean = reinterpret_cast<float*>(w + s.off[7]);
   m->mean_h = reinterpret_cast<float*>(w + s.off[8]);
-  m->loss_part = reinterpret_cast<float*>(w + s.off[9]);
+  m->loss_part = reinterpret_cast<double*>(w + s.off[9]);
   m->loss = reinterpret_cast<double*>(w + s.off[10]);
   m->r = reinterpret_cast<float*>(w + s.off[11]);
   m->a = reinterpret_cast<float*>(w + s.off[12]);
