@@ -68,13 +68,6 @@ def profiled_launch(workload: str, prec: str):
     return tuple(ent["launch"][:2]) if ent else None
 
 
-def profiled_prefetch(workload: str, prec: str) -> int:
-    """Rows in flight (mlf_set_prefetch) of the profiled run: 1 unless the
-    record says otherwise."""
-    ent = _profile_entry(workload, prec)
-    return int(ent["launch"][2]) if ent and len(ent["launch"]) > 2 else 1
-
-
 def measured_traffic(workload: str, prec: str, launch):
     """HBM bytes per launch from rocprofv3 counters, if they were taken on
     the current kernel source in this launch shape (block width, segment
@@ -251,7 +244,7 @@ def ingest_profile(a):
 
     film, _, spec = inputs.workload(a.workload)
     prec = a.precision or spec["precision"]
-    launch = (a.block_w, a.seg_h, a.prefetch or 1)
+    launch = (a.block_w, a.seg_h)
     per = steps_per_launch(film, prec, launch)
     grid = step_grid_threads(film, prec, launch)
     n_lu = film["n_layers"] * film["nx"] * film["ny"]
@@ -309,7 +302,7 @@ def batch_point(args, steps, warm):
     b = mlfilm.Batch([f for f, _ in films], "f32")
     for i, (_, h0) in enumerate(films):
         b.init(i, h0)
-    launch = (*b.autotune(reps=2), b.get_prefetch())
+    launch = b.autotune(reps=2)
     if args.graph_steps:
         b.capture(args.graph_steps)
     print(f"[bench] batch of {len(films)} films, {n_lu / 1e6:.1f} M LU/step, launch {launch}, "
@@ -328,15 +321,14 @@ def batch_point(args, steps, warm):
     del b
 
     # the same films, one single-film kernel launch per film and step: in
-    # the batch's launch shape and rows in flight, and in each film's default
-    # shape (library default); the faster one is the baseline
+    # the batch's launch shape, and in each film's default shape (library
+    # default); the faster one is the baseline
     def plain(batch_shape):
         gs = []
         for f, h0 in films:
             g = mlfilm.Film(f, "f32", check_every=-1)
             if batch_shape:
                 g.set_launch(launch[0], launch[1])
-                g.set_prefetch(launch[3])
             g.init(h0)
             gs.append(g)
         for g in gs:
@@ -358,7 +350,7 @@ def batch_point(args, steps, warm):
     per = steps_per_launch(films[0][0], "f32", launch)  # a launch moves the populations once
     achieved = 72 * n_lu / (kern_ms * per * 1e-3) / 1e9
     out = {
-        "metric": "batched scan: summed layer-lattice updates/s (one launch per step, graph-captured)",
+        "metric": "batched scan: summed layer-lattice updates/s (one launch per pair of steps, graph-captured)",
         "value": value, "unit": "LU/s", "n_gpus": 1, "steps": steps, "warmup": warm,
         "ms_per_step": wall_b * 1e3 / steps, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
@@ -505,7 +497,7 @@ def bench_conv_kernels(args):
 
 
 def batched_block(args):
-    """The batched scan (256 uneven films, FP32, one launch per step) in
+    """The batched scan (256 uneven films, FP32, one launch per pair of steps) in
     the default line: LU/s, its speedup over the films stepped one launch
     each, and its HBM fraction."""
     b = batch_point(args, args.extra_batch_steps, 20)
@@ -550,16 +542,14 @@ def film_point(workload, prec, args, steps, warmup, lattice="d2q9"):
         source = "fixed (D1Q3 kernels)"
     elif (args.block_w or args.seg_h) and workload == args.workload:
         g.set_launch(args.block_w, args.seg_h)
-        g.set_prefetch(args.prefetch)
         source = "given"
     elif pl:
         g.set_launch(*pl)
-        g.set_prefetch(profiled_prefetch(workload, prec))
         source = "autotuned (profiled run)"
     else:
         g.autotune(reps=3)  # library autotuner: times shapes, state unchanged
         source = "autotuned"
-    launch = (*g.get_launch(), g.get_prefetch())
+    launch = g.get_launch()
     print(f"[bench] {workload} {prec} N={film['n_layers']} {film['nx']}x{film['ny']} "
           f"launch={launch} warmup={warmup} steps={steps}", file=sys.stderr, flush=True)
     g.step(warmup)
@@ -583,14 +573,18 @@ def film_point(workload, prec, args, steps, warmup, lattice="d2q9"):
             "per_launch": 1 if d1 or args.rounding == "stochastic" else steps_per_launch(film, prec, launch)}
 
 
-def roofline_block(pt, workload, prec, working_set, copy):
+def roofline_block(pt, workload, prec, working_set, copy, resident=False):
     from paper_2409_16659_amd import mlfilm
 
     bpl = mlfilm.bytes_per_update(prec)
     # one launch of `per` steps reads and writes the populations once
     per = pt["per_launch"]
     achieved = bpl * pt["n_lu"] / (pt["kern_ms"] * per * 1e-3) / 1e9
-    out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    # bandwidth is the measure in every case; what holds a film back is the
+    # vector units where the caches hold it or its storage is 16-bit
+    # (profiles/: instruction counters)
+    bound = "valu" if per == 2 and (resident or prec not in ("f64", "f32")) else "hbm"
+    out = {"bound": bound, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": achieved / HBM_PEAK_GBS,
            "traffic": measured_traffic(workload, prec, pt["launch"]),
            "bytes_per_lu": bpl / per, "lu_per_launch": pt["n_lu"] * per, "kernel_ms": pt["kern_ms"] * per,
@@ -614,9 +608,6 @@ def main():
                     help="launch shape; default: the shape the autotuner chose for the profiled run of this "
                          "kernel source, else the autotuner now")
     ap.add_argument("--seg-h", type=int, default=0, help="launch shape (see --block-w)")
-    ap.add_argument("--prefetch", type=int, default=0,
-                    help="rows in flight in the step kernel with --block-w/--seg-h (0: default, 1 or 2); "
-                         "with --ingest-kt: the profiled run's value")
     ap.add_argument("--autotune", action="store_true", help="always run the autotuner")
     ap.add_argument("--rounding", choices=["nearest", "stochastic"], default="nearest",
                     help="rounding of the stored rest population of --workload (stochastic: f16 / bf16 storage)")
@@ -630,7 +621,7 @@ def main():
     ap.add_argument("--no-copy-ceiling", action="store_true",
                     help="skip timing the streaming copy on buffers of the workloads' sizes")
     ap.add_argument("--batch", action="store_true",
-                    help="batched stability scan instead: 256 uneven films, one launch per step "
+                    help="batched stability scan instead: 256 uneven films, one launch per pair of steps "
                          "(graph-captured, autotuned) against the same films stepped back to back "
                          "through the single-film kernel")
     ap.add_argument("--batch-films", type=int, default=256)
@@ -736,7 +727,7 @@ def main():
         ws = (f"2 x {pop_bytes / 2 ** 20:.0f} MiB population buffers: "
               + ("resident in the 256 MB Infinity Cache (cache-resident point; the HBM-bound point is "
                  "roofline_hbm)" if resident else "HBM-resident"))
-        out["roofline"] = roofline_block(pt, args.workload, prec, ws, copy)
+        out["roofline"] = roofline_block(pt, args.workload, prec, ws, copy, resident)
         if args.hbm_point and args.hbm_point != args.workload:
             hp = args.hbm_point
             hprec = inputs.WORKLOADS[hp]["precision"]

@@ -286,8 +286,9 @@ mlf_status mlf_destroy(mlf_handle* h);
 /* ---- batches of independent films ------------------------------------
  * Many films (the paper's parameter sweeps over wavenumber, tension,
  * contact angle and layer count, Sec. IV) advanced together: every step (or
- * pair of steps, as for one film) is ONE kernel launch over a work list of (film, tile) items, largest
- * film first, with each film's constants in a device table; films may
+ * pair of steps, as for one film) is ONE kernel launch over a work list of
+ * (film, tile) items, most expensive tiles first, with each film's constants
+ * in a device table; films may
  * differ in size, layer count and every physical parameter but share the
  * precision, tau and the wetting exponents.  Results of each film are
  * bit-identical to stepping it alone with the same launch shape.

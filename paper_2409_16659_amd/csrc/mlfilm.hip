@@ -1963,8 +1963,8 @@ mlf_status mlf_friction_matrix_slip(int32_t n, const double* hh, const double* m
 }  // extern "C"
 
 // ============================================================ batches ====
-// Many independent films advanced together: one launch per step over a
-// work list of (film, tile) items, per-film step constants in a device
+// Many independent films advanced together: one launch per step or pair of
+// steps over a work list of (film, tile) items, per-film step constants in a device
 // table, optionally replayed from a captured HIP graph.  Each film is
 // served by an internal single-film handle on its slice of the batch
 // buffers, which provides initialisation, read-back and mass.
@@ -2010,7 +2010,6 @@ struct mlf_batch {
   BatchPlan plan[2];  // of launches of one step, of two (whose segments decide on them)
   int persistent;
   int ahead;  // rows in flight asked for (mlf_batch_set_prefetch; no effect on the kernel)
-  int max_nl;
   hipGraphExec_t graph[2];  // as mlf_handle's
   int graph_steps;
   int64_t steps;
@@ -2367,7 +2366,6 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
   b->cur = 0;
   b->scratch = static_cast<unsigned char*>(scratch);
   b->stream = static_cast<hipStream_t>(stream);
-  b->max_nl = 1;
   size_t off = 0;
   for (int f = 0; f < n; ++f) {
     mlf_handle* h = nullptr;
@@ -2380,7 +2378,6 @@ mlf_status mlf_batch_create(const mlf_params* films, int32_t n, void* pop_a, voi
     b->film.push_back(h);
     b->offset.push_back(off);
     off += film_bytes(&films[f]);
-    b->max_nl = std::max(b->max_nl, films[f].n_layers);
   }
   b->ready.assign(n, false);
   b->order.resize(n);

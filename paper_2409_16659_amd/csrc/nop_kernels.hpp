@@ -47,7 +47,7 @@ __device__ inline float gelu_f(float a, float* dg) {
 }
 
 // Epilogues of the convolution: v = products + bias, then
-//  kEpiPlain: out = v;
+//  kEpiPlain: out = v (mlf_nop_time_conv alone: what the products cost);
 //  kEpiGelu:  out = v (pre-activation, FP32), outb = bf16(gelu(v));
 //  kEpiGeluB: outb = bf16(gelu(v)) only (inference keeps no pre-activation);
 //  kEpiResid: out = res + v, outb = bf16(out)  (residual block output; res

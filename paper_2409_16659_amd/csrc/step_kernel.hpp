@@ -42,8 +42,9 @@
 //    in +y, one lane per column (overlapped tiling: two halo columns on each
 //    side per step).  Neighbours in x come from the neighbouring lanes (DPP
 //    wavefront shifts folded into the subtractions that use them), rows pass
-//    through registers, so wavefronts share nothing and never wait for each
-//    other.  Every row forms its stencil features once (two neighbour
+//    through registers, so wavefronts exchange no data.  Those of a workgroup
+//    meet every two rows, so that the columns neighbouring strips share are
+//    read from L2.  Every row forms its stencil features once (two neighbour
 //    differences per value) instead of nine neighbour reads per node.
 //  * With tau = 1 a step needs only the moments of the row, so a second step
 //    runs on the first one's output without leaving the wavefront: the
@@ -52,12 +53,16 @@
 //    memory once per two steps, for three more halo columns and rows on each
 //    side.  Intermediate values are rounded as their storage would round
 //    them: results do not depend on how steps are paired.
-//  * What bounds it, per step at 4096 x 4096: FP32, 3 layers, memory (4.7 TB/s
-//    of population traffic; 386 us against 750 us for one step per launch
-//    from LDS-tiled workgroups, at 0.93 of the streaming copy); f16mix, 4 layers,
-//    vector arithmetic (449 us against 588 us).  At 1024 x 1024 x 3 FP32, held
-//    by the Infinity Cache, arithmetic and the recomputed rows of its 10-row
-//    segments (29.6 us against 41.1 us).
+//  * What bounds it (two steps per launch; share of the SIMDs' cycles in which a
+//    vector instruction issues, SQ_ACTIVE_INST_VALU): FP32, 3 layers, 4096 x
+//    4096, memory, 4.7 TB/s of population traffic at 0.90 of the streaming copy
+//    with the vector units at 0.67 (386 us per step against 750 us for one step
+//    per launch from LDS-tiled workgroups); f16mix, 4 layers, the vector units,
+//    0.89 (449 us against 588 us); 1024 x 1024 x 3 FP32, held by the Infinity
+//    Cache, 0.65 over the dispatch and 0.81 while its wavefronts run, half of it
+//    on the recomputed rows of 10-row segments (29.6 us against 41.1 us).  FP64
+//    films of three layers (777 x 515) issue in 0.19 of the cycles: one
+//    wavefront per SIMD waits for its own results and loads.
 //  * Moments wait two rows for their collision in the wavefront's own LDS, and
 //    the next row's populations are prefetched into registers as loaded
 //    (unconverted), so that the wait for them falls where they are used.
@@ -1384,7 +1389,8 @@ __device__ inline void batch_tile(const unsigned char* __restrict__ src, unsigne
 }
 
 // One launch advances every film of a batch by STEPS steps.  Work item w
-// (film, group of tiles, one per wavefront) is items[w]; items are ordered largest film first.  With
+// (film, group of tiles, one per wavefront) is items[w]; items are ordered by the
+// cost of a tile, longest first.  With
 // gridDim.x < n_items the workgroups are persistent and take items
 // w = r * gridDim.x + tile_of_block(blockIdx.x, gridDim.x), r = 0, 1, ...;
 // either way consecutive items run on one XCD.  `flip` selects the source

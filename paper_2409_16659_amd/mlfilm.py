@@ -485,8 +485,8 @@ def batch_query_sizes(params_list):
 
 
 class Batch:
-    """Many independent films advanced by one launch per step (C ABI
-    mlf_batch_*).  Films share the storage precision, tau and exponents.
+    """Many independent films advanced by one launch per step or pair of steps
+    (C ABI mlf_batch_*).  Films share the storage precision, tau and exponents.
     Buffers are torch uint8 tensors owned by this object; the batch runs on
     its own (default-priority) stream so that its step loop can be
     captured into a HIP graph."""
