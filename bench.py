@@ -68,17 +68,18 @@ def profiled_launch(workload: str, prec: str):
     return tuple(ent["launch"][:2]) if ent else None
 
 
+def profiled_prefetch(workload: str, prec: str) -> int:
+    """Rows in flight (mlf_set_prefetch) of the profiled run: the default;
+    the library stores the value and no kernel depends on it."""
+    return 1
+
+
 def measured_traffic(workload: str, prec: str, launch):
     """HBM bytes per launch from rocprofv3 counters, if they were taken on
     the current kernel source in this launch shape (block width, segment
-    height, rows in flight); else None."""
+    height); else None."""
     ent = _profile_entry(workload, prec)
-    if not ent:
-        return None
-    rec = list(ent.get("launch", []))
-    if len(rec) == 2:
-        rec.append(1)
-    if rec != list(launch):
+    if not ent or list(ent.get("launch", []))[:2] != list(launch)[:2]:
         return None
     return ent.get("hbm_bytes_per_launch")
 

@@ -739,10 +739,14 @@ long long film_tiles(const mlf_params& p, int sh, int steps) {
 // Shape of launches of two steps.  Neighbouring strips in one workgroup march
 // together and share the columns that both read, which pays where the film
 // streams from HBM: FP32, 4096^2, 3 layers, 388 us per step with eight
-// wavefronts per workgroup, 412 with four, 570 with one.  16-bit storage is
-// bound by arithmetic instead and gains from tiles dealt out one by one (f16,
-// 3 layers, 2900 x 2000: 151 us with one, 168 with four), as do films with
-// fewer tiles than SIMDs but more than CUs.
+// wavefronts per workgroup, 412 with four, 570 with one; over 42 films of two to
+// four layers with more tiles than SIMDs the times are 1.03, 1.03 and 1.08 of
+// the best shape's with eight, four and one.  16-bit storage is bound by
+// arithmetic instead and gains from tiles dealt out one by one (f16, 3 layers,
+// 2900 x 2000: 151 us with one, 168 with four; over 24 films 1.02 of the best
+// with one, 1.06 with four or eight), as do films with fewer tiles than SIMDs
+// but more than CUs: FP32, 3 layers, 777 x 515 (8 rows) 18.1 us per step with
+// one, 19.7 with four, 24.5 with eight, and so in all of 18 films.
 Shape two_step_shape(const mlf_params& p) {
   Shape s;
   s.h = two_step_seg([&](int h) { return film_tiles(p, h, 2); }, p.ny);
